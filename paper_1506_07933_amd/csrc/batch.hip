@@ -458,8 +458,8 @@ int batch_create(mifft_batch* out, int count, const int* dims, int kind, int pre
 static bool plan_groupable(const Plan& P)
 {
     if (P.ws_bytes != 0) return false;
-    for (const Pass& q : P.fwd)
-        if ((q.kind != P_CONTIG && q.kind != P_STRIDED) || (q.src != B_IN && q.src != B_OUT) ||
+    for (const Pass& q : P.exec_fwd())
+        if ((q.kind != P_CONTIG && q.kind != P_STRIDED && q.kind != P_PLANE) || (q.src != B_IN && q.src != B_OUT) ||
             (q.dst != B_IN && q.dst != B_OUT))
             return false;
     return true;
@@ -468,11 +468,11 @@ static bool plan_groupable(const Plan& P)
 static int enqueue_grouped(mifft_batch b, void* const* in, void* const* out, hipStream_t s)
 {
     size_t npass = 0;
-    for (const auto& kv : b->plans) npass = std::max(npass, plan_of(kv.second)->fwd.size());
+    for (const auto& kv : b->plans) npass = std::max(npass, plan_of(kv.second)->exec_fwd().size());
     for (size_t k = 0; k < npass; ++k) {
         for (const auto& kv : b->plans) {
             const Plan* P = plan_of(kv.second);
-            if (k >= P->fwd.size()) continue;
+            if (k >= P->exec_fwd().size()) continue;
             std::vector<int> members;
             for (int t = 0; t < b->count; ++t)
                 if (std::equal(kv.first.begin(), kv.first.end(), b->dims.begin() + 3 * t)) members.push_back(t);
@@ -484,7 +484,7 @@ static int enqueue_grouped(mifft_batch b, void* const* in, void* const* out, hip
                     }
                 continue;
             }
-            const Pass& q = P->fwd[k];
+            const Pass& q = P->exec_fwd()[k];
             for (size_t i = 0; i < members.size();) {
                 const int ng = (int)std::min<size_t>(kMaxGroup, members.size() - i);
                 const void* src[kMaxGroup];

@@ -135,7 +135,8 @@ int mifft_plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int pre
         delete p;
         return rc;
     }
-    if ((flags & MIFFT_TUNE) && (rc = tune_plan(*p))) {
+    // a tuned plan runs the passes that the tuner timed
+    if ((rc = (flags & MIFFT_TUNE) ? tune_plan(*p) : build_planes(*p))) {
         delete p;
         return rc;
     }
@@ -212,7 +213,7 @@ int mifft_plan_create_nd(mifft_plan* out, int rank, const int* dims, int kind, i
             p->cus = cus;
     }
     p->esz = prec == MIFFT_FP64 ? 16 : 8;
-    if ((rc = build_nd(*p, flags))) {
+    if ((rc = build_nd(*p, flags)) || (rc = build_planes(*p))) {
         delete p;
         return rc;
     }
@@ -495,11 +496,11 @@ static int check_exec(mifft_plan plan, const void* in, void* out, void* ws, bool
 // transposed-schedule lists when the call is in place (in == out).
 static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out)
 {
-    return (in == out && !p.fwd_ip.empty()) ? p.fwd_ip : p.fwd;
+    return (in == out && !p.fwd_ip.empty()) ? p.fwd_ip : p.exec_fwd();
 }
 static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out)
 {
-    return (in == out && !p.inv_ip.empty()) ? p.inv_ip : p.inv;
+    return (in == out && !p.inv_ip.empty()) ? p.inv_ip : p.exec_inv();
 }
 
 int mifft_execute_forward_ws(mifft_plan plan, const void* in, void* out, void* ws, void* stream)
@@ -623,10 +624,10 @@ int mifft_spectral_apply(mifft_plan plan, int op, double alpha, const void* f, v
     if (op < MIFFT_OP_POISSON || op > MIFFT_OP_DZ) return set_error(MIFFT_ERR_INVALID, "unknown operator %d", op);
     if ((rc = check_field(f, "f")) || (rc = check_field(u, "u"))) return rc;
     if (f == u) return set_error(MIFFT_ERR_INVALID, "f and u must not overlap");
-    std::vector<Pass> list = plan->poisson;
+    std::vector<Pass> list = plan->exec_poisson();
     for (int k = 0; k < plan->poisson_mul_n; ++k) {
-        list[plan->poisson_mul + k].op = op;
-        list[plan->poisson_mul + k].alpha = alpha;
+        list[plan->exec_mul() + k].op = op;
+        list[plan->exec_mul() + k].alpha = alpha;
     }
     char* w = (char*)(ws ? ws : plan->ws);
     const size_t half = plan->poisson_ws_bytes / 2;
@@ -667,8 +668,8 @@ int mifft_spectral_gradient(mifft_plan plan, const void* f, void* gx, void* gy, 
         for (int k = 0; k < j; ++k)
             if (g[j] == g[k]) return set_error(MIFFT_ERR_INVALID, "the outputs must be distinct");
     }
-    const std::vector<Pass>& P = plan->poisson;
-    const int mi = plan->poisson_mul, nm = plan->poisson_mul_n;
+    const std::vector<Pass>& P = plan->exec_poisson();
+    const int mi = plan->exec_mul(), nm = plan->poisson_mul_n;
     const Pass& M = P[mi];
     const BufId D = M.src;
     const BufId E = M.kind == P_POISSON_X ? (D == B_SEND ? B_RECV : B_SEND) : B_WS;
@@ -704,8 +705,8 @@ int mifft_spectral_divergence(mifft_plan plan, const void* vx, const void* vy, c
         return rc;
     if (d == vx || d == vy || d == vz) return set_error(MIFFT_ERR_INVALID, "d must not overlap the inputs");
     const void* v[3] = {vx, vy, vz};
-    const std::vector<Pass>& P = plan->poisson;
-    const int mi = plan->poisson_mul, nm = plan->poisson_mul_n;
+    const std::vector<Pass>& P = plan->exec_poisson();
+    const int mi = plan->exec_mul(), nm = plan->poisson_mul_n;
     const Pass& M = P[mi];
     const BufId D = M.src;
     char* w = (char*)(ws ? ws : plan->ws);
@@ -882,7 +883,7 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
     if (!is_live(plan)) return set_error(MIFFT_ERR_BADPLAN, "handle is not a live plan");
     static const char* kn[] = {"contig", "contig_pack", "strided", "strided_unpack", "r2c_z",
                                "c2r_z",  "poisson",     "pack",    "unpack",         "copy", "poisson_x",
-                               "strided_pack"};
+                               "strided_pack", "plane", "plane_r2c", "plane_c2r"};
     std::string s;
     auto add = [&](const char* tag, const Pass& q) {
         char line[640];
@@ -927,6 +928,9 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
         for (const Pass& q : plan->poisson) add("poisson", q);
         for (const Pass& q : plan->fwd_ip) add("forward_inplace", q);
         for (const Pass& q : plan->inv_ip) add("inverse_inplace", q);
+        for (const Pass& q : plan->plane_fwd) add("plane_forward", q);
+        for (const Pass& q : plan->plane_inv) add("plane_inverse", q);
+        for (const Pass& q : plan->plane_poisson) add("plane_poisson", q);
     }
     snprintf(buf, len, "%s", s.c_str());
     return MIFFT_OK;

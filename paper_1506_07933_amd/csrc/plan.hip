@@ -471,6 +471,34 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         hipLaunchKernelGGL(fn, dim3(p.grid), dim3(p.block), p.shmem, s, a);
         break;
     }
+    case P_PLANE:
+    case P_PLANE_R2C:
+    case P_PLANE_C2R: {
+        PlaneArgs<T> a{};
+        a.in = src;
+        a.out = dst;
+        for (int i = 0; i < ng && ng > 1; ++i) {
+            a.grp.in[i] = (const V*)gsrc[i];
+            a.grp.out[i] = (V*)gdst[i];
+        }
+        a.twz = (const V*)p.tw;
+        a.tw2 = (const V*)p.tw2;
+        a.twy = (const V*)p.twy;
+        a.ntiles = p.ntiles;
+        a.is_x = p.is_o;
+        a.is_r = p.is_i;
+        a.os_x = p.os_o;
+        a.os_r = p.os_i;
+        a.sgn = (T)p.sgn;
+        a.nt_out = p.nt_out;
+        a.cp = p.cp;
+        auto fn = p.kind == P_PLANE ? v.plane : p.kind == P_PLANE_R2C ? v.plane_r2c : v.plane_c2r;
+        ensure_lds(reinterpret_cast<const void*>(fn), p.shmem);
+        unsigned gx = p.grid;
+        if (ng > 1 && (int)p.grid < p.ntiles) gx = std::max(1u, (p.grid + (unsigned)ng - 1) / (unsigned)ng);
+        hipLaunchKernelGGL(fn, dim3(gx, ng), dim3(p.block), p.shmem, s, a);
+        break;
+    }
     case P_POISSON:
         return launch_spectral<T>((const V*)src, (V*)dst, p.n0, p.n1, p.n2c, p.nz, p.op, (T)p.scale, (T)p.alpha,
                                   p.acc, s);
@@ -487,7 +515,8 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
 hipError_t launch_pass_group(const Pass& p, int prec, int ng, const void* const* src, void* const* dst,
                              hipStream_t s)
 {
-    if (ng < 1 || ng > kMaxGroup || (p.kind != P_CONTIG && p.kind != P_STRIDED)) return hipErrorInvalidValue;
+    if (ng < 1 || ng > kMaxGroup || (p.kind != P_CONTIG && p.kind != P_STRIDED && p.kind != P_PLANE))
+        return hipErrorInvalidValue;
     if (prec == MIFFT_FP64) return launch_fft<double>(p, src[0], dst[0], s, ng, src, dst);
     return launch_fft<float>(p, src[0], dst[0], s, ng, src, dst);
 }
@@ -1103,6 +1132,14 @@ Extent pass_extent(const Pass& p, size_t esz)
         e.in = oi + line_map_extent(p.ni, p.nlines, p.is_o, p.is_i, p.L + 1);
         e.out = oo + line_map_extent(p.ni, p.nlines, p.os_o, p.os_i, p.L);
         break;
+    case P_PLANE: // L (pairs of reals), or the L + 1 of a half spectrum
+    case P_PLANE_R2C:
+    case P_PLANE_C2R: {
+        const long long x = p.ntiles - 1, r = p.cp.A - 1;
+        e.in = oi + x * p.is_o + r * p.is_i + p.L + (p.kind == P_PLANE_C2R);
+        e.out = oo + x * p.os_o + r * p.os_i + p.L + (p.kind == P_PLANE_R2C);
+        break;
+    }
     case P_POISSON:
         e.in = e.out = (long long)p.n0 * p.n1 * p.n2c;
         break;
@@ -1162,7 +1199,8 @@ int validate_extents(const Plan& plan)
         long long in, out;
     } lists[] = {{&plan.fwd, "forward", sig, spec},         {&plan.inv, "inverse", spec, sig},
                  {&plan.poisson, "poisson", sig, sig},         {&plan.fwd_ip, "in-place forward", sig, spec},
-                 {&plan.inv_ip, "in-place inverse", spec, sig}};
+                 {&plan.inv_ip, "in-place inverse", spec, sig}, {&plan.plane_fwd, "plane forward", sig, spec},
+                 {&plan.plane_inv, "plane inverse", spec, sig}, {&plan.plane_poisson, "plane poisson", sig, sig}};
     for (const List& l : lists) {
         for (size_t k = 0; k < l.v->size(); ++k) {
             const Pass& p = (*l.v)[k];
@@ -1668,6 +1706,174 @@ int build_nd(Plan& plan, unsigned /*flags*/)
     plan.poisson.clear();
     plan.poisson_ws_bytes = 0;
     tile_passes(plan);
+    return validate_extents(plan);
+}
+
+// ---------------------------------------------------------- plane passes
+
+// The in-place column transform of A rows.
+static bool col_plan(int prec, int A, ColPlan* cp)
+{
+    const PlaneRadices f = plane_radices(A, prec == MIFFT_FP64);
+    if (f.n == 0) return false;
+    cp->A = A;
+    cp->n = f.n;
+    int q = A;
+    for (int i = 0; i < f.n; ++i) {
+        ColStage& s = cp->s[i];
+        s.R = f.r[i];
+        s.tws = A / q;
+        q /= f.r[i];
+        s.q = q;
+        s.mq = q > 1 ? (uint32_t)(((1ull << 32) + q - 1) / q) : 0;
+    }
+    return true;
+}
+
+static size_t plane_lds(const Plan& plan, int A, int L)
+{
+    return ((size_t)A * plane_pitch(L) + L + A) * plan.esz + 2 * (size_t)A;
+}
+
+static const void* plane_fn(int prec, const Pass& p)
+{
+    return with_table(prec, [&](const auto& t) {
+        const auto& v = t[p.vidx];
+        return reinterpret_cast<const void*>(p.kind == P_PLANE       ? v.plane
+                                             : p.kind == P_PLANE_R2C ? v.plane_r2c
+                                                                     : v.plane_c2r);
+    });
+}
+
+// A plane pass of `tiles` planes of A rows from the z-pass (whose variant and
+// tables it takes); false where the plane does not fit.
+static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool* ok)
+{
+    *ok = false;
+    const size_t lds = plane_lds(plan, A, z.L);
+    p.vidx = find_variant(plan.prec, z.L, 0, 1);
+    if (p.vidx < 0 || A < 2 || lds > kLdsMax || !col_plan(plan.prec, A, &p.cp)) return MIFFT_OK;
+    // A plane is one workgroup's work, and one that leaves no room for a second
+    // on its CU takes 11 us however few there are: those pay only where they
+    // nearly fill the device (FP32, z and y apart against fused, a whole
+    // transform: 64 x 128 x 128 18.5 against 22.0 us, 128 planes 24.6 against
+    // 26.2, 200 planes 39.6 against 36.1, 1024 planes 169 against 115).  Smaller
+    // planes pay at any count (2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64
+    // 15.7 against 13.5).
+    if (2 * lds > kLdsMax && 4LL * tiles < 3LL * plan.cus) return MIFFT_OK;
+    p.kind = z.kind == P_R2C ? P_PLANE_R2C : z.kind == P_C2R ? P_PLANE_C2R : P_PLANE;
+    p.L = z.L;
+    if (!plane_fn(plan.prec, p)) return MIFFT_OK;
+    p.tw = z.tw;
+    p.tw2 = z.tw2;
+    p.sgn = z.sgn;
+    p.tag = 0;
+    int rc = get_twiddles(plan, A, (void**)&p.twy);
+    if (rc) return rc;
+    // 512 threads where two or more workgroups share a CU, but no more
+    // wavefronts than the rows need
+    const int lpw = 64 / zline_threads(z.L, plan.prec == MIFFT_FP64);
+    const int want = (2 * lds <= kLdsMax && tiles >= 2 * plan.cus) ? 512 : 1024;
+    const int waves = std::max(1, std::min(want / 64, (A + lpw - 1) / lpw));
+    p.lines_per_wg = waves * lpw;
+    p.block = (unsigned)(waves * 64);
+    p.shmem = lds;
+    p.ntiles = tiles;
+    // resident grid, balanced as in strided_grid: a workgroup's next tile is
+    // read while its last one is transformed
+    int per_cu = 0;
+    if (!plan.plan_only) {
+        const void* fn = plane_fn(plan.prec, p);
+        ensure_lds(fn, lds);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)p.block, lds) != hipSuccess) {
+            (void)hipGetLastError();
+            per_cu = 0;
+        }
+    }
+    if (per_cu <= 0) per_cu = (int)std::max<size_t>(1, std::min(kLdsMax / lds, (size_t)(2048 / p.block)));
+    const long long cap = (long long)plan.cus * per_cu;
+    p.grid = (unsigned)tiles;
+    if (tiles > cap) {
+        const long long rounds = (tiles + cap - 1) / cap;
+        p.grid = (unsigned)((tiles + rounds - 1) / rounds);
+    }
+    *ok = true;
+    return MIFFT_OK;
+}
+
+// Replace the z- and y-pass at list[k], list[k + 1] (either order) by a plane
+// pass where both work on the same standard layout.
+static int fuse_plane(Plan& plan, std::vector<Pass>& list, size_t k, bool* fused)
+{
+    *fused = false;
+    if (k + 1 >= list.size()) return MIFFT_OK;
+    const Pass& first = list[k];
+    const Pass& second = list[k + 1];
+    auto is_z = [](const Pass& q) { return q.kind == P_CONTIG || q.kind == P_R2C || q.kind == P_C2R; };
+    const bool zfirst = is_z(first);
+    const Pass& z = zfirst ? first : second;
+    const Pass& y = zfirst ? second : first;
+    const bool real = z.kind == P_R2C || z.kind == P_C2R;
+    if (!is_z(z) || z.tag != 0 || y.kind != P_STRIDED || y.tag != 1 || z.nyq_buf != B_NONE || y.lane || z.lane)
+        return MIFFT_OK;
+    // z in line order on both sides, y over rows of the same pitch
+    if (z.ni < z.nlines || y.cols != (real ? z.L + 1 : z.L) || y.es_in != y.es_out || y.gs_in != y.gs_out ||
+        y.gdiv_in > 1 || y.gdiv_out > 1 || y.gs_in != (long long)y.L * y.es_in)
+        return MIFFT_OK;
+    if (first.dst != second.src || first.off_out != second.off_in || (zfirst ? z.os_i : z.is_i) != y.es_in ||
+        z.nlines != (long long)y.L * y.groups || (z.kind == P_R2C && !zfirst) || (z.kind == P_C2R && zfirst))
+        return MIFFT_OK;
+    Pass p;
+    bool ok = false;
+    int rc = make_plane(plan, p, z, y.L, y.groups, &ok);
+    if (rc || !ok) return rc;
+    p.src = first.src;
+    p.off_in = first.off_in;
+    p.dst = second.dst;
+    p.off_out = second.off_out;
+    p.is_i = zfirst ? z.is_i : y.es_in;
+    p.os_i = zfirst ? y.es_out : z.os_i;
+    p.is_o = p.is_i * y.L;
+    p.os_o = p.os_i * y.L;
+    const double out_bytes = (double)p.ntiles * p.os_o * plan.esz;
+    p.nt_out = out_bytes > 256.0 * 1024 * 1024 - 1 ? 1 : 0;
+    list[k] = p;
+    list.erase(list.begin() + (long)k + 1);
+    *fused = true;
+    return MIFFT_OK;
+}
+
+int build_planes(Plan& plan)
+{
+    plan.plane_fwd.clear();
+    plan.plane_inv.clear();
+    plan.plane_poisson.clear();
+    plan.plane_mul = -1;
+    // MIFFT_PLANES=0 and an explicit choice among the one-axis schedules keep those
+    if (const char* e = getenv("MIFFT_PLANES"))
+        if (atoi(e) == 0) return MIFFT_OK;
+    if (getenv("MIFFT_CHUNK_MIB") || getenv("MIFFT_BLOCKED")) return MIFFT_OK;
+    if (plan.pencil || plan.slab) return MIFFT_OK;
+    int rc;
+    bool fused = false;
+    std::vector<Pass> f = plan.fwd, v = plan.inv, po = plan.poisson;
+    if ((rc = fuse_plane(plan, f, 0, &fused))) return rc;
+    if (fused) plan.plane_fwd = f;
+    if (v.size() >= 2) {
+        if ((rc = fuse_plane(plan, v, v.size() - 2, &fused))) return rc;
+        if (fused) plan.plane_inv = v;
+    }
+    const char* unfused = getenv("MIFFT_POISSON_UNFUSED");
+    if (po.size() >= 5 && plan.poisson_mul_n == 1 && !(unfused && atoi(unfused) != 0)) {
+        bool f2 = false;
+        if ((rc = fuse_plane(plan, po, 0, &fused))) return rc;
+        const int mul = plan.poisson_mul - (fused ? 1 : 0);
+        if ((rc = fuse_plane(plan, po, po.size() - 2, &f2))) return rc;
+        if (fused && f2) {
+            plan.plane_poisson = po;
+            plan.plane_mul = mul;
+        }
+    }
     return validate_extents(plan);
 }
 

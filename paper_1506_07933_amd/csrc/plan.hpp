@@ -28,7 +28,10 @@ enum PassKind {
     P_UNPACK,
     P_COPY,
     P_POISSON_X, // fused x-forward, Poisson multiply, x-inverse (in place)
-    P_STRIDED_OSPLIT // strided pass storing through a split (slab pack) map
+    P_STRIDED_OSPLIT, // strided pass storing through a split (slab pack) map
+    P_PLANE,          // z- and y-axis of a plane in LDS (plane.hpp)
+    P_PLANE_R2C,
+    P_PLANE_C2R
 };
 
 // Which caller buffer a pass reads or writes; resolved at execute time.
@@ -85,6 +88,10 @@ struct Pass {
     size_t shmem = 0;
     const void* tw = nullptr;
     const void* tw2 = nullptr;
+    // plane passes: ntiles planes of cp.A rows; row r of plane x at
+    // x * s_o + r * s_i; lines_per_wg rows in work at once
+    ColPlan cp{};
+    const void* twy = nullptr; // length cp.A
 };
 
 struct TuneChoice {
@@ -111,6 +118,14 @@ public:
     // blocked intermediates; an in-place call (in == out) runs these lists,
     // the transposed schedule, instead.  Empty otherwise.
     std::vector<Pass> fwd_ip, inv_ip;
+    // With planes (z and y) that fit LDS: the lists that execute calls run, z
+    // and y fused into one pass; empty where the lists above run as they are.
+    std::vector<Pass> plane_fwd, plane_inv, plane_poisson;
+    int plane_mul = -1; // index of the multiply pass in plane_poisson
+    const std::vector<Pass>& exec_fwd() const { return plane_fwd.empty() ? fwd : plane_fwd; }
+    const std::vector<Pass>& exec_inv() const { return plane_inv.empty() ? inv : plane_inv; }
+    const std::vector<Pass>& exec_poisson() const { return plane_poisson.empty() ? poisson : plane_poisson; }
+    int exec_mul() const { return plane_poisson.empty() ? poisson_mul : plane_mul; }
     int blocked = 0; // block width (columns) of the blocked intermediates, 0: not used
     // pencil stages
     Pass pz, pz_pack, pk, upk, py, py_split;
@@ -216,5 +231,7 @@ void apply_chunking(Plan& plan);  // interleave z/y (x^-1/z^-1) over plane chunk
 int build_pencil(Plan& plan, unsigned flags);
 int build_slab(Plan& plan, unsigned flags);
 int build_nd(Plan& plan, unsigned flags);
+// Fuse the z- and y-passes of a built plan's lists into plane passes (untuned plans).
+int build_planes(Plan& plan);
 
 } // namespace mifft

@@ -1,7 +1,7 @@
 // registry.hpp -- table of compiled kernel variants, per precision.
 #pragma once
 
-#include "kernels.hpp"
+#include "plane.hpp"
 
 namespace mifft {
 
@@ -9,6 +9,7 @@ template <typename T> using ContigFn = void (*)(ContigArgs<T>);
 template <typename T> using StridedFn = void (*)(StridedArgs<T>);
 template <typename T> using RealFn = void (*)(RealArgs<T>);
 template <typename T> using PoissonXFn = void (*)(PoissonXArgs<T>);
+template <typename T> using PlaneFn = void (*)(PlaneArgs<T>);
 
 // One compiled configuration of a line length: its radix policy, the
 // elements-per-thread multiplier and the kernels built from it.
@@ -29,6 +30,10 @@ template <typename T> struct Variant {
     RealFn<T> r2c; // line of 2L reals
     RealFn<T> c2r;
     PoissonXFn<T> poisson_x; // fused x-forward, multiply, x-inverse
+    // z- and y-axis in one pass, z-lines of L (policy 0, emul 1; else null)
+    PlaneFn<T> plane;
+    PlaneFn<T> plane_r2c; // rows of 2L reals
+    PlaneFn<T> plane_c2r;
 };
 
 // All variants of this precision (concatenated over the compiled chunks).

@@ -1,0 +1,104 @@
+"""Plane passes (z- and y-axis of a plane in LDS, one pass): against the oracle
+at the sizes where they can go wrong -- the shortest and longest lines and
+columns, lines that leave lanes of a wavefront idle, rows that do not fill a
+wavefront, one to four column stages, planes near the LDS limit and more
+planes than the device holds at once -- and in place, grouped and inside the
+spectral operators."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1506_07933_amd import synth
+from conftest import TOL, rel_l2
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+C2C = [(3, 2, 2), (1, 3, 4), (5, 125, 100), (2, 250, 10), (1, 8, 15), (3, 8, 512), (2, 18, 486), (200, 128, 128),
+       (2, 81, 48), (10, 1000, 16, 8), (2, 3, 5, 6, 36), (300, 4, 9, 30), (6, 96, 90), (2, 600, 5)]
+
+
+def _plane_lines(p, which):
+    return [line for line in p.describe().splitlines() if line.startswith("plane_" + which)]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", C2C)
+def test_c2c_planes(shape, prec):
+    from paper_1506_07933_amd import Plan
+    cd = np.complex64 if prec == "fp32" else np.complex128
+    x = synth.uniform_complex(shape, cd, seed=sum(shape))
+    p = Plan(shape, "c2c", prec)
+    print("  ", shape, prec, [line.split()[1:4] for line in _plane_lines(p, "forward")], flush=True)
+    xd = torch.from_numpy(x).cuda()
+    X = p.forward(xd)
+    ref = oracle.fftnd_c2c(x.astype(np.complex128), -1)
+    assert rel_l2(X.cpu().numpy(), ref) <= TOL[prec]
+    y = p.inverse(X)
+    assert rel_l2(y.cpu().numpy(), np.prod(shape) * x.astype(np.complex128)) <= TOL[prec]
+    z = xd.clone()
+    p.forward(z, out=z)
+    assert torch.equal(z, X)
+    p.inverse(z, out=z)
+    assert torch.equal(z, y)
+    p.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", [(3, 2, 4), (4, 9, 30), (2, 128, 90), (2, 16, 1024), (200, 100, 192), (1, 64, 64),
+                                   (9, 1000, 15, 18), (3, 4, 10, 50)])
+def test_real_planes(shape, prec):
+    """Forward, and C2R of a spectrum that is not Hermitian (the imaginary
+    parts of its ends do not count); inputs are kept."""
+    from paper_1506_07933_amd import Plan
+    rd = np.float32 if prec == "fp32" else np.float64
+    x = synth.normal_real(shape, rd, seed=sum(shape))
+    p = Plan(shape, "r2c", prec)
+    print("  ", shape, prec, [line.split()[1:4] for line in _plane_lines(p, "forward")], flush=True)
+    xd = torch.from_numpy(x).cuda()
+    Y = p.forward(xd)
+    assert rel_l2(Y.cpu().numpy(), oracle.fftnd_r2c(x.astype(np.float64))) <= TOL[prec]
+    half = shape[:-1] + (shape[-1] // 2 + 1,)
+    h = synth.uniform_complex(half, np.complex64 if prec == "fp32" else np.complex128, seed=7)
+    hd = torch.from_numpy(h).cuda()
+    u = p.inverse(hd)
+    assert rel_l2(u.cpu().numpy(), oracle.fftnd_c2r(h.astype(np.complex128), shape[-1])) <= TOL[prec]
+    np.testing.assert_array_equal(hd.cpu().numpy(), h)
+    np.testing.assert_array_equal(xd.cpu().numpy(), x)
+    p.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", [(8, 6, 4), (40, 48, 100), (1, 16, 36)])
+def test_spectral_operators_on_planes(shape, prec):
+    from paper_1506_07933_amd import Plan
+    rd = np.float32 if prec == "fp32" else np.float64
+    f = synth.normal_real(shape, rd, seed=5)
+    f = (f - f.mean(dtype=np.float64)).astype(rd)
+    p = Plan(shape, "r2c", prec)
+    assert len(_plane_lines(p, "poisson")) == 3
+    fd = torch.from_numpy(f).cuda()
+    assert rel_l2(p.poisson(fd).cpu().numpy(), oracle.poisson_solve(f.astype(np.float64))) <= TOL[prec]
+    g = p.gradient(fd)
+    ref = oracle.gradient(f.astype(np.float64))
+    for j in range(3):
+        if np.linalg.norm(ref[j]) > 0:
+            assert rel_l2(g[j].cpu().numpy(), ref[j]) <= TOL[prec]
+        assert torch.equal(g[j], p.spectral(oracle.OP_DX + j, fd))
+    p.close()
+
+
+def test_grouped_planes_equal_single_ones():
+    """20 members of one shape (two launches of a pass), planes of each."""
+    from paper_1506_07933_amd import BatchPlan, Plan
+    shapes = [(12, 20, 36)] * 20 + [(30, 64, 64)] * 3
+    data = [synth.uniform_complex(s, np.complex64, seed=i) for i, s in enumerate(shapes)]
+    xs = [torch.from_numpy(d).cuda() for d in data]
+    outs = [torch.empty_like(x) for x in xs]
+    b = BatchPlan(shapes, "fp32", mode="grouped")
+    b.forward(xs, outs)
+    for s, x, o in zip(shapes, xs, outs):
+        p = Plan(s, "c2c", "fp32")
+        assert torch.equal(p.forward(x), o)
+        p.close()
+    b.close()
