@@ -455,36 +455,54 @@ int batch_create(mifft_batch* out, int count, const int* dims, int kind, int pre
 // with a pass that is not a plain contiguous / strided pass on the caller's
 // buffers, or that needs a workspace (which the members would share), runs
 // per transform instead.
-static bool plan_groupable(const Plan& P)
+static bool list_groupable(const Plan& P, const std::vector<Pass>& list)
 {
     if (P.ws_bytes != 0) return false;
-    for (const Pass& q : P.exec_fwd())
-        if ((q.kind != P_CONTIG && q.kind != P_STRIDED && q.kind != P_PLANE) || (q.src != B_IN && q.src != B_OUT) ||
-            (q.dst != B_IN && q.dst != B_OUT))
+    for (const Pass& q : list)
+        if ((q.kind != P_CONTIG && q.kind != P_STRIDED && q.kind != P_PLANE && q.kind != P_COLS) ||
+            (q.src != B_IN && q.src != B_OUT) || (q.dst != B_IN && q.dst != B_OUT))
             return false;
     return true;
 }
 
 static int enqueue_grouped(mifft_batch b, void* const* in, void* const* out, hipStream_t s)
 {
+    // the transforms of one shape that run the same list: an in-place one may
+    // run another than the rest (Plan::plane_oop)
+    struct Group {
+        mifft_plan plan;
+        const std::vector<Pass>* list;
+        bool together;
+        std::vector<int> members;
+    };
+    std::vector<Group> groups;
     size_t npass = 0;
-    for (const auto& kv : b->plans) npass = std::max(npass, plan_of(kv.second)->exec_fwd().size());
+    for (const auto& kv : b->plans) {
+        const Plan* P = plan_of(kv.second);
+        Group g[2] = {{kv.second, &P->exec_fwd(), false, {}}, {kv.second, &P->fwd, false, {}}};
+        for (int t = 0; t < b->count; ++t)
+            if (std::equal(kv.first.begin(), kv.first.end(), b->dims.begin() + 3 * t))
+                g[in[t] == out[t] && P->plane_oop].members.push_back(t);
+        for (Group& k : g) {
+            if (k.members.empty()) continue;
+            k.together = list_groupable(*P, *k.list);
+            npass = std::max(npass, k.list->size());
+            groups.push_back(std::move(k));
+        }
+    }
     for (size_t k = 0; k < npass; ++k) {
-        for (const auto& kv : b->plans) {
-            const Plan* P = plan_of(kv.second);
-            if (k >= P->exec_fwd().size()) continue;
-            std::vector<int> members;
-            for (int t = 0; t < b->count; ++t)
-                if (std::equal(kv.first.begin(), kv.first.end(), b->dims.begin() + 3 * t)) members.push_back(t);
-            if (!plan_groupable(*P)) {
+        for (const Group& gr : groups) {
+            if (k >= gr.list->size()) continue;
+            const std::vector<int>& members = gr.members;
+            if (!gr.together) {
                 for (int t : members)
                     if (k == 0) {
-                        int rc = mifft_execute_forward(kv.second, in[t], out[t], s);
+                        int rc = mifft_execute_forward(gr.plan, in[t], out[t], s);
                         if (rc) return rc;
                     }
                 continue;
             }
-            const Pass& q = P->exec_fwd()[k];
+            const Pass& q = (*gr.list)[k];
             for (size_t i = 0; i < members.size();) {
                 const int ng = (int)std::min<size_t>(kMaxGroup, members.size() - i);
                 const void* src[kMaxGroup];

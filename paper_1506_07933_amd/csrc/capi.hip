@@ -494,13 +494,18 @@ static int check_exec(mifft_plan plan, const void* in, void* out, void* ws, bool
 
 // The pass list of a call: plans with the blocked schedule run their
 // transposed-schedule lists when the call is in place (in == out).
-static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out)
+// `own`: the call's workspace is the plan's own.
+static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out, bool own)
 {
-    return (in == out && !p.fwd_ip.empty()) ? p.fwd_ip : p.exec_fwd();
+    if (in != out) return p.exec_fwd();
+    if (!p.plane_fwd_ip.empty()) return own ? p.plane_fwd_ip : p.fwd;
+    return p.fwd_ip.empty() ? p.exec_fwd() : p.fwd_ip;
 }
-static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out)
+static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out, bool own)
 {
-    return (in == out && !p.inv_ip.empty()) ? p.inv_ip : p.exec_inv();
+    if (in != out) return p.exec_inv();
+    if (!p.plane_inv_ip.empty()) return own ? p.plane_inv_ip : p.inv;
+    return p.inv_ip.empty() ? p.exec_inv() : p.inv_ip;
 }
 
 int mifft_execute_forward_ws(mifft_plan plan, const void* in, void* out, void* ws, void* stream)
@@ -508,7 +513,7 @@ int mifft_execute_forward_ws(mifft_plan plan, const void* in, void* out, void* w
     clear_error();
     int rc = check_exec(plan, in, out, ws, true);
     if (rc) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_inverse_ws(mifft_plan plan, const void* in, void* out, void* ws, void* stream)
@@ -516,7 +521,7 @@ int mifft_execute_inverse_ws(mifft_plan plan, const void* in, void* out, void* w
     clear_error();
     int rc = check_exec(plan, in, out, ws, true);
     if (rc) return rc;
-    return run_passes(*plan, inv_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, inv_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_forward(mifft_plan plan, const void* in, void* out, void* stream)
@@ -524,7 +529,7 @@ int mifft_execute_forward(mifft_plan plan, const void* in, void* out, void* stre
     clear_error();
     int rc = check_exec(plan, in, out, nullptr, false);
     if (rc) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out, true), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_inverse(mifft_plan plan, const void* in, void* out, void* stream)
@@ -532,7 +537,7 @@ int mifft_execute_inverse(mifft_plan plan, const void* in, void* out, void* stre
     clear_error();
     int rc = check_exec(plan, in, out, nullptr, false);
     if (rc) return rc;
-    return run_passes(*plan, inv_list(*plan, in, out), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, inv_list(*plan, in, out, true), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 // Forward transform whose workspace is the file-scope device array below
@@ -587,7 +592,7 @@ int mifft_execute_forward_static(mifft_plan plan, const void* in, void* out, voi
                          dev);
     void* ws = nullptr;
     if (plan->ws_bytes && (rc = scratch_address(dev, &ws))) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 static int check_spectral(mifft_plan plan, const void* ws)
@@ -883,10 +888,10 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
     if (!is_live(plan)) return set_error(MIFFT_ERR_BADPLAN, "handle is not a live plan");
     static const char* kn[] = {"contig", "contig_pack", "strided", "strided_unpack", "r2c_z",
                                "c2r_z",  "poisson",     "pack",    "unpack",         "copy", "poisson_x",
-                               "strided_pack", "plane", "plane_r2c", "plane_c2r"};
+                               "strided_pack", "plane", "plane_r2c", "plane_c2r", "cols"};
     std::string s;
     auto add = [&](const char* tag, const Pass& q) {
-        char line[640];
+        char line[768];
         int pol = q.vidx >= 0 ? variant_policy(plan->prec, q.vidx) : -1;
         int tpl = q.vidx >= 0 ? variant_tpl(plan->prec, q.vidx) : 0;
         const bool strided = q.kind == mifft::P_STRIDED || q.kind == mifft::P_STRIDED_SPLIT ||
@@ -895,12 +900,14 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
         snprintf(line, sizeof(line),
                  "%s kind=%s axis=%c L=%d policy=%d tpl=%d sgn=%d lines=%lld lpw=%d B=%d cols=%d groups=%d "
                  "es=%lld/%lld gs=%lld/%lld off=%lld/%lld grid=%u block=%u lds=%zu pf=%d tpg=%d tiles=%d nt=%d "
-                 "nto=%d gdiv=%d/%d gs2=%lld/%lld pm=%u/%lld ni=%d is=%lld/%lld os=%lld/%lld lane=%d%s%s\n",
+                 "nto=%d gdiv=%d/%d gs2=%lld/%lld pm=%u/%lld ni=%d is=%lld/%lld os=%lld/%lld lane=%d nb=%d C=%d "
+                 "rows=%d sb=%lld/%lld ys=%lld/%lld tw=%d%s%s\n",
                  tag, kn[q.kind], "zyx-"[q.tag < 3 ? q.tag : 3], q.L, pol, tpl, q.sgn, q.nlines, q.lines_per_wg,
                  q.B, q.cols, q.groups, q.es_in, q.es_out, q.gs_in, q.gs_out, q.off_in, q.off_out, q.grid,
                  q.block, q.shmem, pf, q.tpg, q.ntiles, q.nt_in, q.nt_out, q.gdiv_in, q.gdiv_out, q.gs2_in,
                  q.gs2_out, q.kind == mifft::P_CONTIG_PACK ? q.fd.d : 0u, q.kind == mifft::P_CONTIG_PACK ? q.blk : 0,
-                 q.ni, q.is_o, q.is_i, q.os_o, q.os_i, q.lane, q.fork_after ? " fork=1" : "",
+                 q.ni, q.is_o, q.is_i, q.os_o, q.os_i, q.lane, q.nb, q.split_C, q.cp ? q.cp->A : 0, q.is_b, q.os_b, q.ys_in,
+                 q.ys_out, q.split_tw, q.fork_after ? " fork=1" : "",
                  q.join_before ? " join=1" : "");
         s += line;
     };

@@ -1,0 +1,289 @@
+// cols.hpp -- the second pass of a transform whose y-axis is split over two.
+//
+// A plane too large for LDS is split along y: n1 = A B, y = y1 + B y2,
+// k1 = ka + A kb.  The plane pass (plane.hpp) transforms z and y2 (A rows of
+// a tile (x, y1)) and multiplies by w_n1^{y1 ka}; this pass transforms y1
+// (B points) and x (L points) of C columns of k2 for one ka, so three axes
+// take two passes over memory.  The C2R runs them in the opposite order: here
+// kb and x first, with the factor w_n1^{y1 ka} on the results.
+//
+// The tile is [x][y1][c] in LDS; the B-point DFTs are taken as the rows are
+// loaded, the x stages run in place as those of plane.hpp do (a row of the
+// x-axis is the B C elements of one x).
+//
+// What bounds it: a tile whose workgroup shares its CU, HBM or the Infinity
+// Cache (256^3 FP32 R2C, 67 + 67 MB: 32 us; the x-pass it replaces, which moved
+// as much, 38 us); a tile alone on its CU, its own phases, although the next
+// tile's loads are in flight meanwhile (2-4%).  Consecutive tiles share cache
+// lines where rows are not whole lines (129 columns) or a tile's rows are
+// half lines; each XCD therefore takes consecutive tiles (256^3 FP32, 64-byte
+// rows: C2C 133 -> 112 us a transform, R2C 87 -> 77).
+#pragma once
+
+#include "plane.hpp"
+
+namespace mifft {
+
+template <typename T> struct ColsArgs {
+    const cx<T>* in;
+    cx<T>* out;
+    GroupPtrs<T> grp;  // grouped launches, as in ContigArgs
+    const cx<T>* tw;   // length L
+    const cx<T>* twn;  // length n1: results times w_n1^{y1 g} (null: not)
+    int ntiles, groups, cols;
+    int B, C;
+    int flat;          // tiles over the flattened (group, column) index, else C columns of one group
+    int tpg;           // tiles per group (not flat)
+    // element x, y1 of column (g, c) at g gs + x es + y1 ys + c on each side
+    long long gs_in, gs_out;
+    uint32_t es_in, ys_in, es_out, ys_out;
+    T sgn;
+    int nt_out, xcd;
+    ColPlan cp;
+};
+
+template <typename T> struct ColsCtx {
+    using V = cx<T>;
+    V* tile;
+    const V* tw;
+    const unsigned short* rev;
+    int tid, nt;       // threads: a multiple of B C
+    int p, c;          // this thread's place in a row of B C, and its column
+    int P, C;
+    int b0, bs;        // first butterfly and step along x
+};
+
+// y1: the B values of (x, c) are loaded, transformed and written to the tile.
+// The loads of a tile of at most kColsHeld bytes per thread are held in
+// registers (`pre`), so they can be issued a tile ahead.
+constexpr int kColsHeld = 128;
+template <typename T> constexpr int cols_slots() { return kColsHeld / (int)sizeof(cx<T>); }
+
+template <typename T, int R>
+__device__ __forceinline__ void cols_load(const ColsCtx<T>& x, const ColsArgs<T>& a, const cx<T>* in, bool valid,
+                                          cx<T>* pre)
+{
+    using V = cx<T>;
+    constexpr int NB = cols_slots<T>() / R;
+    const int L = a.cp.A, bs = x.nt / x.C;
+    const int b0 = x.tid / x.C;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int b = b0 + i * bs;
+        const uint32_t o = (uint32_t)b * a.es_in;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            pre[i * R + r] = V{T(0), T(0)};
+            if (valid && b < L) pre[i * R + r] = *at(in, o + r * a.ys_in);
+        }
+    }
+}
+
+template <typename T, int R>
+__device__ __forceinline__ void cols_first(const ColsCtx<T>& x, const ColsArgs<T>& a, const cx<T>* pre)
+{
+    using V = cx<T>;
+    constexpr int NB = cols_slots<T>() / R;
+    const int L = a.cp.A, bs = x.nt / x.C;
+    const int b0 = x.tid / x.C;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int b = b0 + i * bs;
+        if (b < L) {
+            V v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                v[r] = pre[i * R + r];
+                v[r].y *= a.sgn;
+            }
+            Bfly<R>::fwd(v);
+            V* q = x.tile + b * x.P + x.c;
+#pragma unroll
+            for (int r = 0; r < R; ++r) q[r * x.C] = v[r];
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void cols_load(const ColsCtx<T>& x, const ColsArgs<T>& a, const cx<T>* in, bool valid,
+                                          cx<T>* pre)
+{
+    switch (a.B) {
+    case 2: cols_load<T, 2>(x, a, in, valid, pre); break;
+    case 3: cols_load<T, 3>(x, a, in, valid, pre); break;
+    case 4: cols_load<T, 4>(x, a, in, valid, pre); break;
+    case 5: cols_load<T, 5>(x, a, in, valid, pre); break;
+    case 6: cols_load<T, 6>(x, a, in, valid, pre); break;
+    default: cols_load<T, 8>(x, a, in, valid, pre); break;
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void cols_first(const ColsCtx<T>& x, const ColsArgs<T>& a, const cx<T>* pre)
+{
+    switch (a.B) {
+    case 2: cols_first<T, 2>(x, a, pre); break;
+    case 3: cols_first<T, 3>(x, a, pre); break;
+    case 4: cols_first<T, 4>(x, a, pre); break;
+    case 5: cols_first<T, 5>(x, a, pre); break;
+    case 6: cols_first<T, 6>(x, a, pre); break;
+    default: cols_first<T, 8>(x, a, pre); break;
+    }
+}
+
+// One in-place stage along x; the last one stores to global memory.
+template <typename T, int R, bool LAST>
+__device__ __forceinline__ void cols_stage(const ColsCtx<T>& x, const ColsArgs<T>& a, const ColStage& s, cx<T>* out,
+                                           bool valid, cx<T> w)
+{
+    using V = cx<T>;
+    const int nb = a.cp.A / R, q = s.q, bs = x.bs;
+    int b = x.b0;
+    for (; b < nb; b += bs) {
+        int g = b;
+        if (q > 1) g = (int)__umulhi((uint32_t)b, s.mq);
+        const int off = b - g * q;
+        V* p = x.tile + (g * R * q + off) * x.P + x.p;
+        V v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = p[r * q * x.P];
+        Bfly<R>::fwd(v);
+        if constexpr (LAST) {
+            const int k0 = x.rev[g * R];
+            if (!valid) continue;
+            if (a.twn) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[r] = cmul(v[r], w);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r].y *= a.sgn;
+            const uint32_t o = (uint32_t)k0 * a.es_out;
+            uint32_t step = __builtin_amdgcn_readfirstlane((uint32_t)nb * a.es_out);
+            asm volatile("" : "+s"(step)); // offsets by addition
+            if (a.nt_out) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) store_nt<T>(at(out, o + r * step), v[r]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) *at(out, o + r * step) = v[r];
+            }
+        } else {
+            const int e = off * s.tws;
+            const V* w2 = x.tw;
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[r] = cmul(v[r], *(w2 += e));
+#pragma unroll
+            for (int r = 0; r < R; ++r) p[r * q * x.P] = v[r];
+        }
+    }
+}
+
+template <typename T, bool LAST>
+__device__ __forceinline__ void cols_dispatch(const ColsCtx<T>& x, const ColsArgs<T>& a, ColStage s, cx<T>* out,
+                                              bool valid, cx<T> w)
+{
+    s.q = __builtin_amdgcn_readfirstlane(s.q);
+    s.tws = __builtin_amdgcn_readfirstlane(s.tws);
+    asm volatile("" : "+s"(s.q), "+s"(s.tws)); // as in col_dispatch
+    switch (s.R) {
+    case 2: cols_stage<T, 2, LAST>(x, a, s, out, valid, w); break;
+    case 3: cols_stage<T, 3, LAST>(x, a, s, out, valid, w); break;
+    case 4: cols_stage<T, 4, LAST>(x, a, s, out, valid, w); break;
+    case 5: cols_stage<T, 5, LAST>(x, a, s, out, valid, w); break;
+    case 6: cols_stage<T, 6, LAST>(x, a, s, out, valid, w); break;
+    case 8: cols_stage<T, 8, LAST>(x, a, s, out, valid, w); break;
+    default:
+        if constexpr (sizeof(T) == 4) {
+            if (s.R == 9)
+                cols_stage<T, 9, LAST>(x, a, s, out, valid, w);
+            else if (s.R == 10)
+                cols_stage<T, 10, LAST>(x, a, s, out, valid, w);
+            else if (s.R == 12)
+                cols_stage<T, 12, LAST>(x, a, s, out, valid, w);
+            else if (s.R == 15)
+                cols_stage<T, 15, LAST>(x, a, s, out, valid, w);
+            else if (s.R == 16)
+                cols_stage<T, 16, LAST>(x, a, s, out, valid, w);
+        }
+    }
+}
+
+template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T> a)
+{
+    using V = cx<T>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    V* tile = reinterpret_cast<V*>(smem_raw);
+    const int L = a.cp.A;
+    ColsCtx<T> x;
+    x.tile = tile;
+    x.tid = threadIdx.x;
+    x.nt = blockDim.x;
+    x.C = a.C;
+    x.P = a.B * a.C;
+    x.p = x.tid % x.P;
+    x.c = x.p % a.C;
+    const int y1 = x.p / a.C;
+    x.b0 = x.tid / x.P;
+    x.bs = x.nt / x.P;
+    V* tw = tile + L * x.P;
+    unsigned short* rev = reinterpret_cast<unsigned short*>(tw + L);
+    for (int i = x.tid; i < L; i += x.nt) {
+        tw[i] = a.tw[i];
+        rev[i] = (unsigned short)digit_reverse(a.cp, i);
+    }
+    x.tw = tw;
+    x.rev = rev;
+    // (group, column) of this thread in tile i; false past the last column.
+    // Consecutive workgroups run on different XCDs: each XCD takes a
+    // consecutive run of tiles, so that tiles that share cache lines share an L2.
+    auto locate = [&](int i, int& g, int& col) -> bool {
+        const int t = a.xcd ? (i & 7) * (a.ntiles >> 3) + (i >> 3) : i;
+        if (a.flat) {
+            const uint32_t f = (uint32_t)t * (uint32_t)a.C + (uint32_t)x.c;
+            g = (int)(f / (uint32_t)a.cols);
+            col = (int)(f - (uint32_t)g * (uint32_t)a.cols);
+            return g < a.groups;
+        }
+        g = t / a.tpg;
+        col = (t - g * a.tpg) * a.C + x.c;
+        return col < a.cols;
+    };
+    const V* ain = a.in;
+    V* aout = a.out;
+    if (gridDim.y > 1) {
+        ain = a.grp.in[blockIdx.y];
+        aout = a.grp.out[blockIdx.y];
+    }
+    int i = blockIdx.x;
+    if (i >= a.ntiles) return;
+    int g, col;
+    bool valid = locate(i, g, col);
+    V pre[cols_slots<T>()];
+    cols_load<T>(x, a, ain + (valid ? (long long)g * a.gs_in + col : 0), valid, pre);
+    __syncthreads();
+    for (;;) {
+        asm volatile("" : "+v"(x.tid), "+v"(x.p), "+v"(x.c), "+v"(x.b0)); // as in k_strided
+        cols_first<T>(x, a, pre);
+        V* out = aout + (valid ? (long long)g * a.gs_out + col + (long long)y1 * a.ys_out : 0);
+        V w{T(1), T(0)};
+        if (a.twn && valid) w = a.twn[y1 * g];
+        const int next = i + (int)gridDim.x;
+        bool nvalid = false;
+        if (next < a.ntiles) { // the next tile's loads, in flight during this one's stages
+            nvalid = locate(next, g, col);
+            cols_load<T>(x, a, ain + (nvalid ? (long long)g * a.gs_in + col : 0), nvalid, pre);
+        }
+        __syncthreads();
+        for (int k = 0; k + 1 < a.cp.n; ++k) {
+            cols_dispatch<T, false>(x, a, a.cp.s[k], out, valid, w);
+            __syncthreads();
+        }
+        cols_dispatch<T, true>(x, a, a.cp.s[a.cp.n - 1], out, valid, w);
+        if (next >= a.ntiles) break;
+        __syncthreads(); // the next tile's rows overwrite this one's
+        i = next;
+        valid = nvalid;
+    }
+}
+
+} // namespace mifft

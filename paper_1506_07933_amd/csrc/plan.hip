@@ -485,19 +485,55 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         a.tw2 = (const V*)p.tw2;
         a.twy = (const V*)p.twy;
         a.ntiles = p.ntiles;
+        a.nb = p.nb;
+        a.twn = (const V*)p.twn;
         a.is_x = p.is_o;
+        a.is_b = p.is_b;
         a.is_r = p.is_i;
         a.os_x = p.os_o;
+        a.os_b = p.os_b;
         a.os_r = p.os_i;
         a.sgn = (T)p.sgn;
         a.nt_out = p.nt_out;
-        a.cp = p.cp;
+        a.cp = *p.cp;
         auto fn = p.kind == P_PLANE ? v.plane : p.kind == P_PLANE_R2C ? v.plane_r2c : v.plane_c2r;
         ensure_lds(reinterpret_cast<const void*>(fn), p.shmem);
         unsigned gx = p.grid;
         if (ng > 1 && (int)p.grid < p.ntiles) gx = std::max(1u, (p.grid + (unsigned)ng - 1) / (unsigned)ng);
         hipLaunchKernelGGL(fn, dim3(gx, ng), dim3(p.block), p.shmem, s, a);
         break;
+    }
+    case P_COLS: {
+        ColsArgs<T> a{};
+        a.in = (const V*)src;
+        a.out = (V*)dst;
+        for (int i = 0; i < ng && ng > 1; ++i) {
+            a.grp.in[i] = (const V*)gsrc[i];
+            a.grp.out[i] = (V*)gdst[i];
+        }
+        a.tw = (const V*)p.tw;
+        a.twn = (const V*)p.twn;
+        a.ntiles = p.ntiles;
+        a.groups = p.groups;
+        a.cols = p.cols;
+        a.B = p.nb;
+        a.C = p.split_C;
+        a.flat = p.flat;
+        a.tpg = p.tpg;
+        a.gs_in = p.gs_in;
+        a.gs_out = p.gs_out;
+        a.es_in = (uint32_t)p.es_in;
+        a.ys_in = (uint32_t)p.ys_in;
+        a.es_out = (uint32_t)p.es_out;
+        a.ys_out = (uint32_t)p.ys_out;
+        a.sgn = (T)p.sgn;
+        a.nt_out = p.nt_out;
+        a.xcd = p.ntiles % 8 == 0 && !getenv("MIFFT_NOXCD");
+        a.cp = *p.cp;
+        ensure_lds(cols_kernel(sizeof(T) == 8), p.shmem);
+        unsigned gx = p.grid;
+        if (ng > 1 && (int)p.grid < p.ntiles) gx = std::max(1u, (p.grid + (unsigned)ng - 1) / (unsigned)ng);
+        return launch_cols(a, dim3(gx, ng), p.block, p.shmem, s);
     }
     case P_POISSON:
         return launch_spectral<T>((const V*)src, (V*)dst, p.n0, p.n1, p.n2c, p.nz, p.op, (T)p.scale, (T)p.alpha,
@@ -515,7 +551,8 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
 hipError_t launch_pass_group(const Pass& p, int prec, int ng, const void* const* src, void* const* dst,
                              hipStream_t s)
 {
-    if (ng < 1 || ng > kMaxGroup || (p.kind != P_CONTIG && p.kind != P_STRIDED && p.kind != P_PLANE))
+    if (ng < 1 || ng > kMaxGroup || (p.kind != P_CONTIG && p.kind != P_STRIDED && p.kind != P_PLANE &&
+                                           p.kind != P_COLS))
         return hipErrorInvalidValue;
     if (prec == MIFFT_FP64) return launch_fft<double>(p, src[0], dst[0], s, ng, src, dst);
     return launch_fft<float>(p, src[0], dst[0], s, ng, src, dst);
@@ -540,18 +577,25 @@ int get_twiddles(Plan& plan, int L, void** out)
         *out = it->second;
         return MIFFT_OK;
     }
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, (size_t)L * plan.esz);
-    if (e != hipSuccess) return set_error(MIFFT_ERR_NOMEM, "hipMalloc of %d twiddles: %s", L,
-                                          hipGetErrorString(e));
+    const size_t bytes = ((size_t)L * plan.esz + 255) / 256 * 256;
+    hipError_t e = hipSuccess;
+    if (plan.tw_blocks.empty() || plan.tw_used + bytes > plan.tw_size) {
+        void* block = nullptr;
+        const size_t size = std::max<size_t>(bytes, 64 * 1024); // four tables of the longest lines
+        e = hipMalloc(&block, size);
+        if (e != hipSuccess) return set_error(MIFFT_ERR_NOMEM, "hipMalloc of %d twiddles: %s", L,
+                                              hipGetErrorString(e));
+        plan.tw_blocks.push_back(block);
+        plan.tw_used = 0;
+        plan.tw_size = size;
+    }
+    void* p = (char*)plan.tw_blocks.back() + plan.tw_used;
+    plan.tw_used += bytes;
     if (plan.prec == MIFFT_FP64)
         e = launch_twiddles<double>((cx<double>*)p, L, nullptr);
     else
         e = launch_twiddles<float>((cx<float>*)p, L, nullptr);
-    if (e != hipSuccess) {
-        hipFree(p);
-        return set_error(MIFFT_ERR_DEVICE, "twiddle kernel: %s", hipGetErrorString(e));
-    }
+    if (e != hipSuccess) return set_error(MIFFT_ERR_DEVICE, "twiddle kernel: %s", hipGetErrorString(e));
     plan.twiddles[L] = p;
     *out = p;
     return MIFFT_OK;
@@ -565,7 +609,7 @@ Plan::~Plan()
         if (l.join) hipEventDestroy(l.join);
     }
     for (hipEvent_t e : prof_events) hipEventDestroy(e);
-    for (auto& kv : twiddles) hipFree(kv.second);
+    for (void* b : tw_blocks) hipFree(b);
     if (ws) hipFree(ws);
 }
 
@@ -1135,9 +1179,15 @@ Extent pass_extent(const Pass& p, size_t esz)
     case P_PLANE: // L (pairs of reals), or the L + 1 of a half spectrum
     case P_PLANE_R2C:
     case P_PLANE_C2R: {
-        const long long x = p.ntiles - 1, r = p.cp.A - 1;
-        e.in = oi + x * p.is_o + r * p.is_i + p.L + (p.kind == P_PLANE_C2R);
-        e.out = oo + x * p.os_o + r * p.os_i + p.L + (p.kind == P_PLANE_R2C);
+        const long long x = p.ntiles / p.nb - 1, b = p.nb - 1, r = p.cp->A - 1;
+        e.in = oi + x * p.is_o + b * p.is_b + r * p.is_i + p.L + (p.kind == P_PLANE_C2R);
+        e.out = oo + x * p.os_o + b * p.os_b + r * p.os_i + p.L + (p.kind == P_PLANE_R2C);
+        break;
+    }
+    case P_COLS: {
+        const long long g = p.groups - 1, x = p.cp->A - 1, y = p.nb - 1;
+        e.in = oi + g * p.gs_in + x * p.es_in + y * p.ys_in + p.cols;
+        e.out = oo + g * p.gs_out + x * p.es_out + y * p.ys_out + p.cols;
         break;
     }
     case P_POISSON:
@@ -1191,7 +1241,7 @@ int validate_extents(const Plan& plan)
     const long long half = (long long)plan.n0 * plan.n1 * (plan.n2 / 2 + 1);
     const long long sig = real ? N / 2 : N;   // signal side, complex units
     const long long spec = real ? half : N;   // spectrum side
-    const long long ws = (long long)(plan.ws_bytes / esz);
+    const long long ws = (long long)(plan.ws_bytes / esz), own = (long long)(plan.default_ws_bytes / esz);
     const long long pw = (long long)(plan.poisson_ws_bytes / 2 / esz);
     struct List {
         const std::vector<Pass>* v;
@@ -1200,13 +1250,16 @@ int validate_extents(const Plan& plan)
     } lists[] = {{&plan.fwd, "forward", sig, spec},         {&plan.inv, "inverse", spec, sig},
                  {&plan.poisson, "poisson", sig, sig},         {&plan.fwd_ip, "in-place forward", sig, spec},
                  {&plan.inv_ip, "in-place inverse", spec, sig}, {&plan.plane_fwd, "plane forward", sig, spec},
-                 {&plan.plane_inv, "plane inverse", spec, sig}, {&plan.plane_poisson, "plane poisson", sig, sig}};
+                 {&plan.plane_inv, "plane inverse", spec, sig}, {&plan.plane_poisson, "plane poisson", sig, sig},
+                 {&plan.plane_fwd_ip, "plane in-place forward", sig, spec},
+                 {&plan.plane_inv_ip, "plane in-place inverse", spec, sig}};
     for (const List& l : lists) {
         for (size_t k = 0; k < l.v->size(); ++k) {
             const Pass& p = (*l.v)[k];
             const Extent e = pass_extent(p, plan.esz);
+            const bool ip = l.v == &plan.plane_fwd_ip || l.v == &plan.plane_inv_ip;
             auto cap = [&](BufId b) -> long long {
-                return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? ws : (b == B_SEND || b == B_RECV) ? pw : 0;
+                return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? (ip ? own : ws) : (b == B_SEND || b == B_RECV) ? pw : 0;
             };
             if ((p.src != B_NONE && e.in > cap(p.src)) || (p.dst != B_NONE && e.out > cap(p.dst)))
                 return set_error(MIFFT_ERR_INVALID,
@@ -1712,10 +1765,14 @@ int build_nd(Plan& plan, unsigned /*flags*/)
 // ---------------------------------------------------------- plane passes
 
 // The in-place column transform of A rows.
-static bool col_plan(int prec, int A, ColPlan* cp)
+static const ColPlan* col_plan(Plan& plan, int A)
 {
-    const PlaneRadices f = plane_radices(A, prec == MIFFT_FP64);
-    if (f.n == 0) return false;
+    for (const ColPlan& c : plan.col_plans)
+        if (c.A == A) return &c;
+    const PlaneRadices f = plane_radices(A, plan.prec == MIFFT_FP64);
+    if (f.n == 0) return nullptr;
+    plan.col_plans.push_back(ColPlan{});
+    ColPlan* cp = &plan.col_plans.back();
     cp->A = A;
     cp->n = f.n;
     int q = A;
@@ -1727,12 +1784,12 @@ static bool col_plan(int prec, int A, ColPlan* cp)
         s.q = q;
         s.mq = q > 1 ? (uint32_t)(((1ull << 32) + q - 1) / q) : 0;
     }
-    return true;
+    return cp;
 }
 
 static size_t plane_lds(const Plan& plan, int A, int L)
 {
-    return ((size_t)A * plane_pitch(L) + L + A) * plan.esz + 2 * (size_t)A;
+    return ((size_t)A * plane_pitch(L, plan.prec == MIFFT_FP64) + L + 2 * (size_t)A + (A + 3) / 4) * plan.esz; // tile, tables (plane.hpp)
 }
 
 static const void* plane_fn(int prec, const Pass& p)
@@ -1745,14 +1802,35 @@ static const void* plane_fn(int prec, const Pass& p)
     });
 }
 
+// Resident grid over p.ntiles, balanced as in strided_grid (a plane pass reads
+// a workgroup's next tile while its last one is transformed).
+static void resident_grid(const Plan& plan, Pass& p, const void* fn)
+{
+    int per_cu = 0;
+    if (!plan.plan_only) {
+        ensure_lds(fn, p.shmem);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)p.block, p.shmem) != hipSuccess) {
+            (void)hipGetLastError();
+            per_cu = 0;
+        }
+    }
+    if (per_cu <= 0) per_cu = (int)std::max<size_t>(1, std::min(kLdsMax / p.shmem, (size_t)(2048 / p.block)));
+    const long long cap = (long long)plan.cus * per_cu;
+    p.grid = (unsigned)p.ntiles;
+    if (p.ntiles > cap) {
+        const long long rounds = (p.ntiles + cap - 1) / cap;
+        p.grid = (unsigned)((p.ntiles + rounds - 1) / rounds);
+    }
+}
+
 // A plane pass of `tiles` planes of A rows from the z-pass (whose variant and
 // tables it takes); false where the plane does not fit.
-static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool* ok)
+static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool split, bool* ok)
 {
     *ok = false;
     const size_t lds = plane_lds(plan, A, z.L);
     p.vidx = find_variant(plan.prec, z.L, 0, 1);
-    if (p.vidx < 0 || A < 2 || lds > kLdsMax || !col_plan(plan.prec, A, &p.cp)) return MIFFT_OK;
+    if (p.vidx < 0 || A < 2 || lds > kLdsMax || !(p.cp = col_plan(plan, A))) return MIFFT_OK;
     // A plane is one workgroup's work, and one that leaves no room for a second
     // on its CU takes 11 us however few there are: those pay only where they
     // nearly fill the device (FP32, z and y apart against fused, a whole
@@ -1760,7 +1838,7 @@ static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool
     // 26.2, 200 planes 39.6 against 36.1, 1024 planes 169 against 115).  Smaller
     // planes pay at any count (2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64
     // 15.7 against 13.5).
-    if (2 * lds > kLdsMax && 4LL * tiles < 3LL * plan.cus) return MIFFT_OK;
+    if (!split && 2 * lds > kLdsMax && 4LL * tiles < 3LL * plan.cus) return MIFFT_OK;
     p.kind = z.kind == P_R2C ? P_PLANE_R2C : z.kind == P_C2R ? P_PLANE_C2R : P_PLANE;
     p.L = z.L;
     if (!plane_fn(plan.prec, p)) return MIFFT_OK;
@@ -1771,32 +1849,16 @@ static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool
     int rc = get_twiddles(plan, A, (void**)&p.twy);
     if (rc) return rc;
     // 512 threads where two or more workgroups share a CU, but no more
-    // wavefronts than the rows need
+    // wavefronts than the rows, or eight elements per thread, need
     const int lpw = 64 / zline_threads(z.L, plan.prec == MIFFT_FP64);
     const int want = (2 * lds <= kLdsMax && tiles >= 2 * plan.cus) ? 512 : 1024;
-    const int waves = std::max(1, std::min(want / 64, (A + lpw - 1) / lpw));
+    const int need = std::max((A + lpw - 1) / lpw, A * z.L / 256);
+    const int waves = std::max(1, std::min(want / 64, need));
     p.lines_per_wg = waves * lpw;
     p.block = (unsigned)(waves * 64);
     p.shmem = lds;
     p.ntiles = tiles;
-    // resident grid, balanced as in strided_grid: a workgroup's next tile is
-    // read while its last one is transformed
-    int per_cu = 0;
-    if (!plan.plan_only) {
-        const void* fn = plane_fn(plan.prec, p);
-        ensure_lds(fn, lds);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)p.block, lds) != hipSuccess) {
-            (void)hipGetLastError();
-            per_cu = 0;
-        }
-    }
-    if (per_cu <= 0) per_cu = (int)std::max<size_t>(1, std::min(kLdsMax / lds, (size_t)(2048 / p.block)));
-    const long long cap = (long long)plan.cus * per_cu;
-    p.grid = (unsigned)tiles;
-    if (tiles > cap) {
-        const long long rounds = (tiles + cap - 1) / cap;
-        p.grid = (unsigned)((tiles + rounds - 1) / rounds);
-    }
+    resident_grid(plan, p, plane_fn(plan.prec, p));
     *ok = true;
     return MIFFT_OK;
 }
@@ -1825,7 +1887,7 @@ static int fuse_plane(Plan& plan, std::vector<Pass>& list, size_t k, bool* fused
         return MIFFT_OK;
     Pass p;
     bool ok = false;
-    int rc = make_plane(plan, p, z, y.L, y.groups, &ok);
+    int rc = make_plane(plan, p, z, y.L, y.groups, false, &ok);
     if (rc || !ok) return rc;
     p.src = first.src;
     p.off_in = first.off_in;
@@ -1843,12 +1905,193 @@ static int fuse_plane(Plan& plan, std::vector<Pass>& list, size_t k, bool* fused
     return MIFFT_OK;
 }
 
+// ------------------------------------------------------- split y-axis
+
+// n1 = A B of a split y-axis and C, the columns of a tile of the second pass.
+struct Split {
+    int A = 0, B = 0, C = 0;
+};
+
+static size_t cols_lds(const Plan& plan, int B, int C)
+{
+    return ((size_t)plan.n0 * B * C + plan.n0) * plan.esz + 2 * (size_t)plan.n0;
+}
+
+// Threads of a columns tile: a multiple of its row B C, 512 where two share a
+// CU, enough that each holds its share of the tile in registers; 0: none.
+static int cols_threads(const Plan& plan, int B, int C, long long tiles)
+{
+    const int P = B * C, slots = kColsHeld / (int)plan.esz / B; // rows of C per thread
+    for (int want : {512, 1024}) {
+        if (want == 512 && (2 * cols_lds(plan, B, C) > kLdsMax || tiles <= plan.cus)) continue;
+        const int t = std::min(want, plan.n0 * P) / P * P;
+        if (t > 0 && slots * (t / C) >= plan.n0) return t;
+    }
+    return 0;
+}
+
+// The split with the least estimated time of its two passes, relative to
+// passes whose tiles share a CU (and overlap) and whose rows are whole
+// 128-byte lines; false where three passes are as good.  Measured (three
+// passes against two, us): all shared, 16 x 256 KiB rows: 128 x 256 x 256 FP32
+// 82 -> 61; the plane alone on its CU: 256^3 FP32 C2C 152 -> 115, R2C 95 -> 72;
+// both alone, 128-byte rows: 256^3 FP64 R2C 180 -> 137, C2R 152 -> 137; both
+// alone, 64-byte rows: 256^3 FP64 C2C 297 -> 330, 1024 x 64 x 512 FP32 323 -> 328;
+// 64-byte rows that straddle lines: 500 x 200 x 180 FP32 210 -> 225.
+static bool choose_split(const Plan& plan, int L, int nc, Split* s)
+{
+    int fb = 0, fc = 0; // MIFFT_SPLIT=B,C: that split where it fits (comparison, tests)
+    if (const char* e = getenv("MIFFT_SPLIT")) sscanf(e, "%d,%d", &fb, &fc);
+    double best = fb ? 1e9 : 2.35;
+    bool found = false;
+    for (int B : {2, 3, 4, 5, 6, 8}) {
+        if (plan.n1 % B || plan.n1 / B < 2 || (fb && B != fb)) continue;
+        const size_t pl = plane_lds(plan, plan.n1 / B, L);
+        for (int C : {32, 16, 8, 4}) {
+            const int row = C * (int)plan.esz;
+            const size_t cl = cols_lds(plan, B, C);
+            if ((fc ? C != fc : row < 64 || row > 256) || pl > kLdsMax || cl > kLdsMax || !cols_threads(plan, B, C, (long long)plan.n1 / B * nc / C))
+                continue;
+            const double rows = row >= 128 ? 1.0 : (size_t)nc * plan.esz % 128 == 0 ? 1.1 : 1.25;
+            const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (2 * cl > kLdsMax ? 1.2 : 1.0) * rows;
+            if (cost < best) {
+                best = cost;
+                *s = Split{plan.n1 / B, B, C};
+                found = true;
+            }
+        }
+    }
+    return found;
+}
+
+// The plane pass (x, y1) over z and y2 and the columns pass over y1 and x.
+// With the transposed intermediate's workspace: W[ka][x][y1][k2] forward,
+// W[x][y1][ka][k2] for C2R.  Plans without it go through the output, ka at
+// row ka + A y1 (the columns pass then works in place); an in-place call runs
+// the same passes through the plan's own workspace, which gives the same bits.
+// Their C2R has a workspace of the half spectrum.
+static int build_split(Plan& plan)
+{
+    const int n0 = plan.n0, n1 = plan.n1;
+    const bool real = plan.kind == MIFFT_R2C;
+    const bool W = plan.transposed;
+    const int nc = real ? plan.n2 / 2 + 1 : plan.n2, ncw = W ? plan.ncw : nc;
+    if (plan.nd || n0 < 2 || n1 < 4 || plan.n2 < 2) return MIFFT_OK;
+    Split sp;
+    const int L = real ? plan.n2 / 2 : plan.n2;
+    if (L < 2 || !choose_split(plan, L, nc, &sp)) return MIFFT_OK;
+    const int A = sp.A, B = sp.B;
+    // Without the workspace's large strides three passes are at their best:
+    // 128^3 C2C FP32 24.3 us against 27.4, 128 x 128 x 64 FP64 24.3 against 26.8;
+    // other lengths 100^3 24.7 against 20.7, 128 x 160 x 150 48.7 against 37.6, and
+    // 128^3 FP64 R2C 35.7 against 29.3; a columns tile alone on its CU: 125^3 35.1
+    // against 37.8.
+    auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
+    if (!W && !getenv("MIFFT_SPLIT") &&
+        (2 * cols_lds(plan, B, sp.C) > kLdsMax || (!real && pow2(n1) && pow2(plan.n2))))
+        return MIFFT_OK;
+    const long long plane = (long long)n1 * nc;
+    // 32-bit offsets inside a tile
+    if ((unsigned long long)n0 * n1 * ncw * plan.esz >= (1ull << 32)) return MIFFT_OK;
+    Pass z;
+    int rc = real ? make_real_z(plan, z, P_R2C, (long long)n0 * n1)
+                  : make_contig(plan, z, plan.n2, (long long)n0 * n1, contig_variant(plan.prec, plan.n2));
+    if (rc) return rc;
+    const long long zl = L; // row of the caller's z-side array
+    for (int dir = 0; dir < 2; ++dir) {
+        const bool c2r = real && dir == 1;
+        Pass a, c;
+        Pass zd = z;
+        if (c2r) zd.kind = P_C2R;
+        zd.sgn = real ? +1 : dir ? -1 : +1;
+        bool ok = false;
+        if (!(dir ? plan.plane_inv : plan.plane_fwd).empty()) continue;
+        if ((rc = make_plane(plan, a, zd, A, n0 * B, true, &ok)) || !ok) return rc;
+        a.nb = B;
+        c.kind = P_COLS;
+        c.L = n0;
+        c.nb = B;
+        c.split_C = sp.C;
+        if (!(c.cp = col_plan(plan, n0))) return MIFFT_OK;
+        if ((rc = get_twiddles(plan, n0, (void**)&c.tw))) return rc;
+        void* twn = nullptr;
+        if ((rc = get_twiddles(plan, n1, &twn))) return rc;
+        c.sgn = dir ? -1 : +1;
+        c.tag = 2;
+        c.cols = nc;
+        c.groups = A;
+        if (!c2r) {
+            a.src = B_IN;
+            a.dst = B_WS;
+            a.twn = twn;
+            a.split_tw = 1;
+            a.is_o = (long long)n1 * zl;
+            a.is_b = zl;
+            a.is_i = B * zl;
+            a.os_i = W ? (long long)n0 * B * ncw : nc;
+            a.os_o = W ? (long long)B * ncw : plane;
+            a.os_b = W ? ncw : (long long)A * nc;
+            if (!W) a.dst = B_OUT;
+            if (!W && !real) plan.plane_oop = true;
+            c.src = a.dst;
+            c.dst = B_OUT;
+            c.gs_in = a.os_i;
+            c.es_in = a.os_o;
+            c.ys_in = a.os_b;
+            c.gs_out = nc;
+            c.es_out = plane;
+            c.ys_out = (long long)A * nc;
+        } else {
+            c.src = B_IN;
+            c.dst = B_WS;
+            c.twn = twn;
+            c.split_tw = 1;
+            c.gs_in = nc;
+            c.es_in = plane;
+            c.ys_in = (long long)A * nc;
+            c.gs_out = ncw;
+            c.es_out = (long long)n1 * ncw;
+            c.ys_out = (long long)A * ncw;
+            a.src = B_WS;
+            a.dst = B_OUT;
+            a.is_i = ncw;
+            a.is_b = (long long)A * ncw;
+            a.is_o = (long long)n1 * ncw;
+            a.os_o = (long long)n1 * zl;
+            a.os_b = zl;
+            a.os_i = B * zl;
+        }
+        c.flat = c.gs_in == c.cols || c.gs_out == c.cols;
+        c.tpg = (nc + sp.C - 1) / sp.C;
+        c.ntiles = c.flat ? (int)(((long long)A * nc + sp.C - 1) / sp.C) : A * c.tpg;
+        c.shmem = cols_lds(plan, B, sp.C);
+        c.block = (unsigned)cols_threads(plan, B, sp.C, (long long)A * nc / sp.C);
+        const size_t out_bytes = (size_t)n0 * plane * plan.esz;
+        a.nt_out = c2r && out_bytes >= ((size_t)128 << 20);
+        c.nt_out = out_bytes > ((size_t)256 << 20);
+        resident_grid(plan, c, cols_kernel(plan.prec == MIFFT_FP64));
+        (dir ? plan.plane_inv : plan.plane_fwd) = c2r ? std::vector<Pass>{c, a} : std::vector<Pass>{a, c};
+        if (plan.plane_oop) {
+            a.dst = c.src = B_WS;
+            a.os_i = c.gs_in = (long long)n0 * B * nc;
+            a.os_o = c.es_in = (long long)B * nc;
+            a.os_b = c.ys_in = nc;
+            (dir ? plan.plane_inv_ip : plan.plane_fwd_ip) = {a, c};
+            plan.default_ws_bytes = std::max(plan.default_ws_bytes, out_bytes);
+        }
+    }
+    return MIFFT_OK;
+}
+
 int build_planes(Plan& plan)
 {
     plan.plane_fwd.clear();
     plan.plane_inv.clear();
     plan.plane_poisson.clear();
     plan.plane_mul = -1;
+    plan.plane_oop = false;
+    plan.plane_fwd_ip.clear();
+    plan.plane_inv_ip.clear();
     // MIFFT_PLANES=0 and an explicit choice among the one-axis schedules keep those
     if (const char* e = getenv("MIFFT_PLANES"))
         if (atoi(e) == 0) return MIFFT_OK;
@@ -1857,12 +2100,16 @@ int build_planes(Plan& plan)
     int rc;
     bool fused = false;
     std::vector<Pass> f = plan.fwd, v = plan.inv, po = plan.poisson;
-    if ((rc = fuse_plane(plan, f, 0, &fused))) return rc;
-    if (fused) plan.plane_fwd = f;
-    if (v.size() >= 2) {
+    if (getenv("MIFFT_SPLIT") && (rc = build_split(plan))) return rc;
+    if (plan.plane_fwd.empty()) {
+        if ((rc = fuse_plane(plan, f, 0, &fused))) return rc;
+        if (fused) plan.plane_fwd = f;
+    }
+    if (v.size() >= 2 && plan.plane_inv.empty()) {
         if ((rc = fuse_plane(plan, v, v.size() - 2, &fused))) return rc;
         if (fused) plan.plane_inv = v;
     }
+    if ((rc = build_split(plan))) return rc;
     const char* unfused = getenv("MIFFT_POISSON_UNFUSED");
     if (po.size() >= 5 && plan.poisson_mul_n == 1 && !(unfused && atoi(unfused) != 0)) {
         bool f2 = false;

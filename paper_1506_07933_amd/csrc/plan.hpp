@@ -6,6 +6,7 @@
 
 #include <cstdarg>
 #include <cstdint>
+#include <list>
 #include <map>
 #include <mutex>
 #include <string>
@@ -31,7 +32,8 @@ enum PassKind {
     P_STRIDED_OSPLIT, // strided pass storing through a split (slab pack) map
     P_PLANE,          // z- and y-axis of a plane in LDS (plane.hpp)
     P_PLANE_R2C,
-    P_PLANE_C2R
+    P_PLANE_C2R,
+    P_COLS            // y1 and x of a split y-axis (cols.hpp)
 };
 
 // Which caller buffer a pass reads or writes; resolved at execute time.
@@ -88,10 +90,16 @@ struct Pass {
     size_t shmem = 0;
     const void* tw = nullptr;
     const void* tw2 = nullptr;
-    // plane passes: ntiles planes of cp.A rows; row r of plane x at
+    // plane passes: ntiles planes of cp->A rows; row r of plane x at
     // x * s_o + r * s_i; lines_per_wg rows in work at once
-    ColPlan cp{};
-    const void* twy = nullptr; // length cp.A
+    const ColPlan* cp = nullptr; // in Plan::col_plans
+    const void* twy = nullptr; // length cp->A
+    // split y-axis: plane tiles (x, b) of nb per x, rows b s_b apart; the
+    // columns pass takes nb points of y1 and split_C columns of k2 per tile
+    int nb = 1, split_C = 0, flat = 0;
+    int split_tw = 0; // results take the factors w_n1^{y1 ka}
+    long long is_b = 0, os_b = 0, ys_in = 0, ys_out = 0;
+    const void* twn = nullptr; // length n1
 };
 
 struct TuneChoice {
@@ -122,6 +130,11 @@ public:
     // and y fused into one pass; empty where the lists above run as they are.
     std::vector<Pass> plane_fwd, plane_inv, plane_poisson;
     int plane_mul = -1; // index of the multiply pass in plane_poisson
+    // plane_fwd / plane_inv of a C2C plan run out of place only; in place the
+    // same passes go through the plan's own workspace (these lists), or, in
+    // calls that bring their own (of ws_bytes, which is 0), fwd / inv run
+    bool plane_oop = false;
+    std::vector<Pass> plane_fwd_ip, plane_inv_ip;
     const std::vector<Pass>& exec_fwd() const { return plane_fwd.empty() ? fwd : plane_fwd; }
     const std::vector<Pass>& exec_inv() const { return plane_inv.empty() ? inv : plane_inv; }
     const std::vector<Pass>& exec_poisson() const { return plane_poisson.empty() ? poisson : plane_poisson; }
@@ -139,7 +152,12 @@ public:
     bool nd = false;
     std::vector<int> dims;
     Pass sz, sy, sy_pack, spk, sx, sxi, supk, syi, syi_unpack, szi;
-    std::map<int, void*> twiddles; // length -> device table
+    std::map<int, void*> twiddles; // length -> device table, in tw_blocks
+    // device memory of the tables, taken in blocks that hold several (a plan has
+    // three to five: one allocation instead of one each)
+    std::vector<void*> tw_blocks;
+    size_t tw_used = 0, tw_size = 0; // of the last block
+    std::list<ColPlan> col_plans;
     void* ws = nullptr;
     size_t ws_bytes = 0;         // workspace an execute call needs
     size_t default_ws_bytes = 0; // size of the plan's own workspace (covers Poisson too)
@@ -233,5 +251,9 @@ int build_slab(Plan& plan, unsigned flags);
 int build_nd(Plan& plan, unsigned flags);
 // Fuse the z- and y-passes of a built plan's lists into plane passes (untuned plans).
 int build_planes(Plan& plan);
+
+const void* cols_kernel(bool fp64);
+hipError_t launch_cols(const ColsArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
+hipError_t launch_cols(const ColsArgs<double>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
 
 } // namespace mifft

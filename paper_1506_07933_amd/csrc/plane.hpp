@@ -59,9 +59,12 @@ template <typename T> struct PlaneArgs {
     const cx<T>* tw2;     // real: exp(-2 pi i k / n2)
     const cx<T>* twy;     // columns, length A
     int ntiles;
-    // row r of tile x at x * s_x + r * s_r on each side (complex elements;
-    // pairs of reals on a real side)
-    long long is_x, is_r, os_x, os_r;
+    // Tile t is (x, b) = (t / nb, t % nb), its row r at x s_x + b s_b + r s_r on
+    // each side (complex elements; pairs of reals on a real side).  nb > 1: the
+    // y-axis is split (cols.hpp); forward results take w_n1^{b k} from twn.
+    int nb;
+    const cx<T>* twn;
+    long long is_x, is_b, is_r, os_x, os_b, os_r;
     T sgn;                // C2C: +1 forward, -1 inverse
     int nt_out;           // streaming stores
     ColPlan cp;
@@ -72,7 +75,7 @@ __device__ __forceinline__ int digit_reverse(const ColPlan& cp, int p)
 {
     int k = 0, mul = 1;
     for (int i = 0; i < cp.n; ++i) {
-        const int d = p / cp.s[i].q;
+        const int d = cp.s[i].q > 1 ? (int)__umulhi((uint32_t)p, cp.s[i].mq) : p;
         p -= d * cp.s[i].q;
         k += d * mul;
         mul *= cp.s[i].R;
@@ -236,10 +239,17 @@ constexpr int zline_threads(int L, bool fp64)
     return (nbf + per - 1) / per;
 }
 
+// Between its stages a line keeps one spare place every 2^shift elements.  One
+// exchange (two stages): every 16, which still spreads the first stage's
+// writes, R apart, over the banks; more: every 8 (the second exchange's runs
+// of 8: 1024 x 64 x 512 with 512 = 8 8 8 took 307 us, 344 with one every 16).
+constexpr int line_shift(int L, bool fp64) { return plane_radices(L, fp64).n <= 2 ? 4 : 3; }
+
 template <typename T, int L> struct ZShape {
     static constexpr PlaneRadices f = plane_radices(L, sizeof(T) == 8);
     static constexpr int TPL = zline_threads(L, sizeof(T) == 8);
     static constexpr int LPW = 64 / TPL; // lines per wavefront
+    static constexpr int SH = line_shift(L, sizeof(T) == 8);
     static constexpr int R0 = f.r[0];
     static constexpr int SLOTS = ((L / R0 + TPL - 1) / TPL) * R0;
 };
@@ -257,6 +267,8 @@ template <typename T> struct ColCtx {
     uint32_t rs;
     T sgn;
     bool nt;
+    const V* twb;                // COL_STORE: row k times twb[k] (b > 0), in LDS
+    int b;
 };
 
 // C columns of rows of PITCH elements.  Global offsets within a tile fit 32
@@ -286,9 +298,12 @@ __device__ __forceinline__ void col_stage(const ColCtx<T>& x, const ColStage& s,
         V* p = x.tile + (g * R * q + off) * PITCH + c;
         V v[R];
         if constexpr (MODE == COL_LOAD) {
+            const uint32_t o = (uint32_t)off * x.rs + (uint32_t)c; // the first stage: g = 0
+            uint32_t step = __builtin_amdgcn_readfirstlane((uint32_t)q * x.rs);
+            asm volatile("" : "+s"(step));
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                v[r] = *at(x.in, (uint32_t)(off + r * q) * x.rs + (uint32_t)c); // the first stage: g = 0
+                v[r] = *at(x.in, o + r * step);
                 v[r].y *= x.sgn;
             }
         } else {
@@ -298,20 +313,28 @@ __device__ __forceinline__ void col_stage(const ColCtx<T>& x, const ColStage& s,
         Bfly<R>::fwd(v);
         if constexpr (MODE == COL_STORE) { // the last stage: q = 1
             const int k0 = x.rev[g * R];
+            if (x.b > 0) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                V* o = at(x.out, (uint32_t)(k0 + r * nb) * x.rs + (uint32_t)c);
-                v[r].y *= x.sgn;
-                if (x.nt)
-                    store_nt<T>(o, v[r]);
-                else
-                    *o = v[r];
+                for (int r = 0; r < R; ++r) v[r] = cmul(v[r], x.twb[k0 + r * nb]);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r].y *= x.sgn;
+            const uint32_t o = (uint32_t)k0 * x.rs + (uint32_t)c;
+            uint32_t step = __builtin_amdgcn_readfirstlane((uint32_t)nb * x.rs);
+            asm volatile("" : "+s"(step)); // offsets by addition
+            if (x.nt) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) store_nt<T>(at(x.out, o + r * step), v[r]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) *at(x.out, o + r * step) = v[r];
             }
         } else {
             if (q > 1) {
                 const int e = off * s.tws;
+                const V* w = x.tw;
 #pragma unroll
-                for (int r = 1; r < R; ++r) v[r] = cmul(v[r], x.tw[e * r]);
+                for (int r = 1; r < R; ++r) v[r] = cmul(v[r], *(w += e));
             } else { // the last stage, left in the tile
 #pragma unroll
                 for (int r = 0; r < R; ++r) v[r].y *= x.sgn;
@@ -323,8 +346,13 @@ __device__ __forceinline__ void col_stage(const ColCtx<T>& x, const ColStage& s,
 }
 
 template <typename T, int C, int PITCH, int MODE>
-__device__ __forceinline__ void col_dispatch(const ColCtx<T>& x, const ColStage& s, int A)
+__device__ __forceinline__ void col_dispatch(const ColCtx<T>& x, ColStage s, int A)
 {
+    // nothing of a stage is worked out ahead of the tile loop (for all radices at once)
+    s.q = __builtin_amdgcn_readfirstlane(s.q);
+    s.tws = __builtin_amdgcn_readfirstlane(s.tws);
+    A = __builtin_amdgcn_readfirstlane(A);
+    asm volatile("" : "+s"(s.q), "+s"(s.tws), "+s"(A));
     switch (s.R) {
     case 2: col_stage<T, 2, C, PITCH, MODE>(x, s, A); break;
     case 3: col_stage<T, 3, C, PITCH, MODE>(x, s, A); break;
@@ -352,24 +380,27 @@ __device__ __forceinline__ void col_dispatch(const ColCtx<T>& x, const ColStage&
 
 // The Stockham stages of fft_engine.hpp for a line whose threads are in one
 // wavefront, in one row of the tile.  Between the stages the line sits at
-// padded places (lds_pad); its first stage may read and its last stage
-// writes unpadded ones, as the columns do.  Where the padding of a thread's
+// padded places (line_pad, see line_shift); its first stage may read and its last stage writes unpadded
+// ones, as the columns do.  Where the padding of a thread's
 // elements differs by compile-time constants, so do its LDS addresses.
-template <int STEP> __device__ __forceinline__ int pad_read(int j, int r) // lds_pad(j + r STEP)
+template <int SH> __device__ __forceinline__ int line_pad(int idx) { return idx + (idx >> SH); }
+template <int SH, int STEP> __device__ __forceinline__ int pad_read(int j, int r) // line_pad(j + r STEP)
 {
-    if constexpr (STEP % 8 == 0)
-        return lds_pad(j) + r * (STEP / 8 * 9);
+    constexpr int G = 1 << SH;
+    if constexpr (STEP % G == 0)
+        return line_pad<SH>(j) + r * (STEP / G * (G + 1));
     else
-        return lds_pad(j + r * STEP);
+        return line_pad<SH>(j + r * STEP);
 }
-template <int Ns, int R> __device__ __forceinline__ int pad_write(int a, int k, int r) // lds_pad(a Ns R + k + r Ns), k < Ns
+template <int SH, int Ns, int R> __device__ __forceinline__ int pad_write(int a, int k, int r) // line_pad(a Ns R + k + r Ns), k < Ns
 {
-    if constexpr ((Ns * R) % 8 == 0 && 8 % Ns == 0)
-        return a * (Ns * R / 8 * 9) + k + r * Ns + ((r * Ns) >> 3);
-    else if constexpr (Ns % 8 == 0)
-        return lds_pad(a * (Ns * R) + k) + r * (Ns / 8 * 9);
+    constexpr int G = 1 << SH;
+    if constexpr ((Ns * R) % G == 0 && G % Ns == 0)
+        return a * (Ns * R / G * (G + 1)) + k + r * Ns + ((r * Ns) >> SH);
+    else if constexpr (Ns % G == 0)
+        return line_pad<SH>(a * (Ns * R) + k) + r * (Ns / G * (G + 1));
     else
-        return lds_pad(a * (Ns * R) + k + r * Ns);
+        return line_pad<SH>(a * (Ns * R) + k + r * Ns);
 }
 
 template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
@@ -390,7 +421,7 @@ template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
                     if constexpr (FIRST)
                         v[i][r] = c.first_get(i * R + r, j + r * NBF);
                     else
-                        v[i][r] = c.row[pad_read<NBF>(j, r)];
+                        v[i][r] = c.row[pad_read<Z::SH, NBF>(j, r)];
                 }
             }
         }
@@ -412,7 +443,7 @@ template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
                     if constexpr (LAST)
                         c.final_put(j + r * NBF, v[i][r]);
                     else
-                        c.row[pad_write<Ns, R>(a, k, r)] = v[i][r];
+                        c.row[pad_write<Z::SH, Ns, R>(a, k, r)] = v[i][r];
                 }
             }
         }
@@ -506,7 +537,7 @@ __device__ __forceinline__ void plane_tables(const PlaneArgs<T>& a, int L, cx<T>
 }
 
 // Row pitch of the tile: a line's padded places, or its L + 1 outputs.
-constexpr int plane_pitch(int L) { return lds_padded_len(L); }
+constexpr int plane_pitch(int L, bool fp64) { return L + (L >> line_shift(L, fp64)) + 1; }
 
 // Rows of a wavefront: LPW lines at a time; lanes past the last line repeat
 // the first line's threads (same values to the same places), and so do rows
@@ -533,7 +564,7 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
                                               cx<T>* __restrict__ aout)
 {
     using V = cx<T>;
-    constexpr int C = REAL ? L + 1 : L, PITCH = plane_pitch(L);
+    constexpr int C = REAL ? L + 1 : L, PITCH = plane_pitch(L, sizeof(T) == 8);
     extern __shared__ __align__(16) unsigned char smem_raw[];
     V* tile = reinterpret_cast<V*>(smem_raw);
     const int A = a.cp.A;
@@ -543,8 +574,12 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
     ZForward<T, L> c;
     c.t = zr.t;
     c.sgn = REAL ? T(1) : a.sgn;
-    if (zr.first < A) c.load(ain + (long long)x * a.is_x + (long long)zr.row(zr.first, A) * a.is_r);
+    auto in_of = [&](int t) { return ain + (long long)(t / a.nb) * a.is_x + (long long)(t % a.nb) * a.is_b; };
+    const V* in = in_of(x);
+    if (zr.first < A) c.load(in + (long long)zr.row(zr.first, A) * a.is_r);
     ColCtx<T> cc;
+    V* twb = tile + A * PITCH + L + A + (A + 3) / 4; // after the digit reversal
+    cc.twb = twb;
     cc.tile = tile;
     cc.rs = (uint32_t)a.os_r;
     cc.sgn = REAL ? T(1) : a.sgn;
@@ -554,11 +589,14 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
     __syncthreads();
     for (;;) {
         const int xn = x + (int)gridDim.x;
+        const V* next_in = xn < a.ntiles ? in_of(xn) : in;
+        cc.b = x % a.nb;
+        if (cc.b > 0)
+            for (int i = threadIdx.x; i < A; i += blockDim.x) twb[i] = a.twn[cc.b * i];
         for (int r0 = zr.first; r0 < A; r0 += zr.step) {
             const bool last = r0 + zr.step >= A;
             c.has_next = !last || xn < a.ntiles;
-            c.nin = ain + (long long)(last ? xn : x) * a.is_x +
-                    (long long)zr.row(last ? zr.first : r0 + zr.step, A) * a.is_r;
+            c.nin = (last ? next_in : in) + (long long)zr.row(last ? zr.first : r0 + zr.step, A) * a.is_r;
             c.row = tile + zr.row(r0, A) * PITCH;
             // as in k_strided: no address of this is kept across the loops
             asm volatile("" : "+v"(c.t));
@@ -580,7 +618,7 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
             }
         }
         __syncthreads();
-        cc.out = aout + (long long)x * a.os_x;
+        cc.out = aout + (long long)(x / a.nb) * a.os_x + (long long)cc.b * a.os_b;
         for (int i = 0; i + 1 < a.cp.n; ++i) {
             col_dispatch<T, C, PITCH, COL_LDS>(cc, a.cp.s[i], A);
             __syncthreads();
@@ -589,6 +627,7 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
         if (xn >= a.ntiles) break;
         __syncthreads(); // the next tile's rows overwrite this one's
         x = xn;
+        in = next_in;
     }
 }
 
@@ -614,7 +653,7 @@ template <typename T, int L>
 __global__ __launch_bounds__(1024) void k_plane_c2r(PlaneArgs<T> a)
 {
     using V = cx<T>;
-    constexpr int C = L + 1, PITCH = plane_pitch(L);
+    constexpr int C = L + 1, PITCH = plane_pitch(L, sizeof(T) == 8);
     extern __shared__ __align__(16) unsigned char smem_raw[];
     V* tile = reinterpret_cast<V*>(smem_raw);
     const int A = a.cp.A;
@@ -631,10 +670,13 @@ __global__ __launch_bounds__(1024) void k_plane_c2r(PlaneArgs<T> a)
     cc.sgn = T(-1); // the inverse along the columns: conj(F(conj(.)))
     cc.nt = false;
     cc.out = nullptr;
+    cc.twb = nullptr;
+    cc.b = 0;
     plane_tables<T>(a, L, tile + A * PITCH, cc, c.twd);
     __syncthreads();
     for (int x = blockIdx.x; x < a.ntiles; x += gridDim.x) {
-        cc.in = ain + (long long)x * a.is_x;
+        cc.in = ain + (long long)(x / a.nb) * a.is_x + (long long)(x % a.nb) * a.is_b;
+        V* out = aout + (long long)(x / a.nb) * a.os_x + (long long)(x % a.nb) * a.os_b;
         col_dispatch<T, C, PITCH, COL_LOAD>(cc, a.cp.s[0], A);
         __syncthreads();
         for (int i = 1; i < a.cp.n; ++i) {
@@ -645,7 +687,7 @@ __global__ __launch_bounds__(1024) void k_plane_c2r(PlaneArgs<T> a)
             const int row = zr.row(r0, A);
             c.row = tile + row * PITCH;
             asm volatile("" : "+v"(c.t));
-            c.out = aout + (long long)x * a.os_x + (long long)cc.rev[row] * a.os_r;
+            c.out = out + (long long)cc.rev[row] * a.os_r;
             ZStage<T, L, 0, 1, decltype(c)>::run(c);
         }
         if (x + (int)gridDim.x < a.ntiles) __syncthreads();

@@ -1,7 +1,7 @@
 // registry.hpp -- table of compiled kernel variants, per precision.
 #pragma once
 
-#include "plane.hpp"
+#include "cols.hpp"
 
 namespace mifft {
 

@@ -102,3 +102,60 @@ def test_grouped_planes_equal_single_ones():
         assert torch.equal(p.forward(x), o)
         p.close()
     b.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("split,shape", [("2,16", (6, 8, 12)), ("3,16", (5, 12, 18)), ("4,8", (40, 8, 20)), ("5,8", (3, 100, 10)),
+                                         ("6,16", (9, 24, 8)), ("8,8", (125, 32, 6)), ("4,8", (30, 256, 128)),
+                                         ("8,4", (2, 512, 64)), ("2,32", (2, 4, 2))])
+def test_split_planes(monkeypatch, split, shape, prec):
+    """Every B of a split y-axis, through the workspace and through the output,
+    ragged column tiles: C2C in both directions (in place: the one-axis passes
+    or the same bits), R2C, and C2R of a spectrum that is not Hermitian."""
+    from paper_1506_07933_amd import Plan
+    monkeypatch.setenv("MIFFT_SPLIT", split)
+    cd, rd = (np.complex64, np.float32) if prec == "fp32" else (np.complex128, np.float64)
+    x = synth.uniform_complex(shape, cd, seed=sum(shape))
+    p = Plan(shape, "c2c", prec)
+    print("  ", shape, prec, [line.split()[1:4] for line in _plane_lines(p, "forward")], flush=True)
+    assert any("kind=cols" in line for line in _plane_lines(p, "forward"))
+    xd = torch.from_numpy(x).cuda()
+    X = p.forward(xd)
+    ref = oracle.fftnd_c2c(x.astype(np.complex128), -1)
+    assert rel_l2(X.cpu().numpy(), ref) <= TOL[prec]
+    np.testing.assert_array_equal(xd.cpu().numpy(), x)
+    n = float(np.prod(shape))
+    assert rel_l2(p.inverse(X).cpu().numpy(), n * x.astype(np.complex128)) <= TOL[prec]
+    z = xd.clone()
+    p.forward(z, out=z)
+    assert rel_l2(z.cpu().numpy(), ref) <= TOL[prec]
+    p.inverse(z, out=z)
+    assert rel_l2(z.cpu().numpy(), n * x.astype(np.complex128)) <= TOL[prec]
+    p.close()
+    if shape[2] < 4:
+        return
+    p = Plan(shape, "r2c", prec)
+    r = synth.normal_real(shape, rd, seed=3)
+    Y = p.forward(torch.from_numpy(r).cuda())
+    assert rel_l2(Y.cpu().numpy(), oracle.fftnd_r2c(r.astype(np.float64))) <= TOL[prec]
+    h = synth.uniform_complex(shape[:-1] + (shape[-1] // 2 + 1,), cd, seed=7)
+    hd = torch.from_numpy(h).cuda()
+    assert rel_l2(p.inverse(hd).cpu().numpy(), oracle.fftnd_c2r(h.astype(np.complex128), shape[-1])) <= TOL[prec]
+    np.testing.assert_array_equal(hd.cpu().numpy(), h)
+    p.close()
+
+
+def test_grouped_split_planes(monkeypatch):
+    """Grouped launches of both passes, with some transforms in place (those
+    run the one-axis passes)."""
+    from paper_1506_07933_amd import BatchPlan
+    monkeypatch.setenv("MIFFT_SPLIT", "4,8")
+    shapes = [(12, 20, 36)] * 19
+    data = [synth.uniform_complex(s, np.complex64, seed=i) for i, s in enumerate(shapes)]
+    xs = [torch.from_numpy(d).cuda() for d in data]
+    outs = [x if i % 4 == 1 else torch.empty_like(x) for i, x in enumerate(xs)]
+    b = BatchPlan(shapes, "fp32", mode="grouped")
+    b.forward(xs, outs)
+    for d, o in zip(data, outs):
+        assert rel_l2(o.cpu().numpy(), oracle.fft3d_c2c(d.astype(np.complex128), -1)) <= TOL["fp32"]
+    b.close()

@@ -1,0 +1,144 @@
+"""The plane and split schedules on the CPU (MIFFT_PLAN_ONLY): the index maps
+of their passes, followed with a library FFT per line, compose to the 3-D DFT
+for every split, with and without the workspace, in both directions and for
+real data; every plan over a range of shapes keeps its passes inside its
+buffers (the library checks each at plan time)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_1506_07933_amd._lib import MIFFT_PLAN_ONLY, lib
+from paper_1506_07933_amd.fft import plan_describe, plan_destroy
+
+
+def _lists(shape, kind, prec):
+    h = ctypes.c_void_p()
+    assert lib.mifft_plan_create(ctypes.byref(h), *shape, kind, prec, MIFFT_PLAN_ONLY) == 0, lib.mifft_last_error()
+    text = plan_describe(h.value)
+    ws = lib.mifft_workspace_bytes(h.value)
+    plan_destroy(h.value)
+    out = {}
+    for line in text.splitlines():
+        d = dict(kv.split("=") for kv in line.split()[1:])
+        for k, v in d.items():
+            if "/" in v:
+                d[k] = tuple(int(x) for x in v.split("/"))
+            elif v.lstrip("-").isdigit():
+                d[k] = int(v)
+        out.setdefault(line.split()[0], []).append(d)
+    return out, ws // (16 if prec else 8)
+
+
+def _dft(x, sgn, axis):
+    return np.fft.fft(x, axis=axis) if sgn > 0 else np.fft.ifft(x, axis=axis) * x.shape[axis]
+
+
+def _plane(p, src, dst, n1):
+    """Rows (x, b, r) of L points (pairs of reals on a real side)."""
+    A, nb, L, kind = p["rows"], p["nb"], p["L"], p["kind"]
+    c_in, c_out = L + (kind == "plane_c2r"), L + (kind == "plane_r2c")
+    sgn = -1 if kind == "plane_c2r" else (1 if kind == "plane_r2c" else p["sgn"])
+    for t in range(p["tiles"]):
+        x, b = divmod(t, nb)
+        rows = [src[x * p["is"][0] + b * p["sb"][0] + r * p["is"][1]:][:c_in] for r in range(A)]
+        v = np.array(rows)
+        if kind == "plane_r2c":
+            v = np.fft.rfft(np.stack([v.real, v.imag], -1).reshape(A, 2 * L), axis=1)
+        elif kind == "plane":
+            v = _dft(v, sgn, 1)
+        v = _dft(v, sgn, 0)
+        if kind == "plane_c2r":
+            v = np.fft.irfft(v, 2 * L, axis=1) * (2 * L)
+            v = v[:, 0::2] + 1j * v[:, 1::2]
+        if p["tw"]:
+            v = v * np.exp(-2j * np.pi * sgn * b * np.arange(A) / n1)[:, None]
+        for k in range(A):
+            o = x * p["os"][0] + b * p["sb"][1] + k * p["os"][1]
+            dst[o:o + c_out] = v[k]
+
+
+def _cols(p, src, dst, n1):
+    L, B = p["rows"], p["nb"]
+    out = []
+    for g in range(p["groups"]):
+        at = lambda i: [[g * p["gs"][i] + x * p["es"][i] + y * p["ys"][i] for y in range(B)] for x in range(L)]  # noqa: E731
+        idx = np.array(at(0))[:, :, None] + np.arange(p["cols"])
+        v = _dft(_dft(src[idx], p["sgn"], 1), p["sgn"], 0)
+        if p["tw"]:
+            v = v * np.exp(-2j * np.pi * p["sgn"] * np.arange(B) * g / n1)[None, :, None]
+        out.append((np.array(at(1))[:, :, None] + np.arange(p["cols"]), v))
+    for idx, v in out:
+        dst[idx] = v
+
+
+def _strided(p, src, dst):
+    for g in range(p["groups"]):
+        idx = lambda i: g * p["gs"][i] + np.arange(p["L"])[:, None] * p["es"][i] + np.arange(p["cols"])  # noqa: E731
+        dst[idx(1)] = _dft(src[idx(0)], p["sgn"], 0)
+
+
+def _run(passes, bufs, order, n1):
+    for p, (s, d) in zip(passes, order):
+        if p["kind"] == "cols":
+            _cols(p, bufs[s], bufs[d], n1)
+        elif p["kind"] == "strided":
+            _strided(p, bufs[s], bufs[d])
+        else:
+            _plane(p, bufs[s], bufs[d], n1)
+
+
+SPLITS = [("2,16", (6, 8, 12)), ("3,16", (5, 12, 16)), ("4,8", (4, 8, 20)), ("5,8", (3, 20, 10)), ("6,16", (9, 24, 8)),
+          ("8,8", (5, 32, 6)), ("4,8", (3, 256, 128)), ("8,4", (2, 512, 64))]
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("split,shape", SPLITS)
+def test_split_maps_compose_to_the_3d_dft(monkeypatch, split, shape, kind):
+    monkeypatch.setenv("MIFFT_SPLIT", split)
+    n0, n1, n2 = shape
+    nc = n2 // 2 + 1 if kind else n2
+    lists, ws = _lists(shape, kind, 1)
+    fwd, inv = lists.get("plane_forward"), lists.get("plane_inverse")
+    assert fwd and inv
+    rng = np.random.default_rng(3)
+    size = max(n0 * n1 * n2, n0 * n1 * nc)
+    via = "ws" if fwd[0]["os"][1] > nc else "out"  # ka n0 B rows apart in the workspace, adjacent in the output
+    x = rng.standard_normal(shape) if kind else rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    flat = (x.reshape(-1, 2) @ [1, 1j]) if kind else x.reshape(-1)
+    bufs = {"in": flat.astype(complex), "out": np.zeros(size, complex), "ws": np.zeros(max(ws, size), complex)}
+    order = [("in", via), (via, "out")]
+    _run(fwd, bufs, order, n1)
+    ref = np.fft.rfftn(x) if kind else np.fft.fftn(x)
+    got = bufs["out"][:n0 * n1 * nc].reshape(n0, n1, nc)
+    assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
+    bufs = {"in": ref.reshape(-1).copy(), "out": np.zeros(size, complex), "ws": np.zeros(max(ws, size), complex)}
+    _run(inv, bufs, [("in", "ws"), ("ws", "out")] if kind else order, n1)
+    got = bufs["out"][:n0 * n1 * n2 // (2 if kind else 1)]
+    want = flat * (n0 * n1 * n2)
+    assert np.linalg.norm(got - want) <= 1e-12 * np.linalg.norm(want)
+
+
+def test_every_plan_stays_inside_its_buffers():
+    """Lengths of every kind on each axis (the library rejects a pass that
+    reaches past a buffer)."""
+    lens = (2, 3, 8, 15, 25, 48, 64, 90, 100, 125, 128, 162, 200, 243, 256, 300, 384, 500, 512, 1000, 1024)
+    for i, n1 in enumerate(lens):
+        for j, n2 in enumerate(lens):
+            n0 = lens[(3 * i + 5 * j) % len(lens)]
+            for kind in (0, 1):
+                if kind and n2 % 2:
+                    continue
+                for prec in (0, 1):
+                    _lists((n0, n1, n2), kind, prec)
+
+
+def test_switches_keep_the_one_axis_passes(monkeypatch):
+    for env in ("MIFFT_CHUNK_MIB", "MIFFT_BLOCKED", "MIFFT_PLANES"):
+        monkeypatch.setenv(env, "0")
+        lists, _ = _lists((64, 64, 64), 1, 0)
+        assert not [k for k in lists if k.startswith("plane_")]
+        monkeypatch.delenv(env)
+    lists, _ = _lists((64, 64, 64), 1, 0)
+    assert [p["kind"] for p in lists["plane_forward"]] == ["plane_r2c", "strided"]
+    assert [p["kind"] for p in lists["plane_poisson"]] == ["plane_r2c", "poisson_x", "plane_c2r"]
