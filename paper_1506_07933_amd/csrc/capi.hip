@@ -630,7 +630,7 @@ int mifft_spectral_apply(mifft_plan plan, int op, double alpha, const void* f, v
     if ((rc = check_field(f, "f")) || (rc = check_field(u, "u"))) return rc;
     if (f == u) return set_error(MIFFT_ERR_INVALID, "f and u must not overlap");
     std::vector<Pass> list = plan->exec_poisson();
-    for (int k = 0; k < plan->poisson_mul_n; ++k) {
+    for (int k = 0; k < plan->exec_mul_n(); ++k) {
         list[plan->exec_mul() + k].op = op;
         list[plan->exec_mul() + k].alpha = alpha;
     }
@@ -674,12 +674,13 @@ int mifft_spectral_gradient(mifft_plan plan, const void* f, void* gx, void* gy, 
             if (g[j] == g[k]) return set_error(MIFFT_ERR_INVALID, "the outputs must be distinct");
     }
     const std::vector<Pass>& P = plan->exec_poisson();
-    const int mi = plan->exec_mul(), nm = plan->poisson_mul_n;
+    const int mi = plan->exec_mul(), nm = plan->exec_mul_n();
     const Pass& M = P[mi];
     const BufId D = M.src;
-    const BufId E = M.kind == P_POISSON_X ? (D == B_SEND ? B_RECV : B_SEND) : B_WS;
+    const bool split = M.kind == P_COLS_MID; // two spectra of spec_bytes instead of the halves
+    const BufId E = M.kind == P_POISSON_X || split ? (D == B_SEND ? B_RECV : B_SEND) : B_WS;
     char* w = (char*)(ws ? ws : plan->ws);
-    const size_t half = plan->poisson_ws_bytes / 2;
+    const size_t half = split ? plan->spec_bytes : plan->poisson_ws_bytes / 2;
     hipStream_t s = (hipStream_t)stream;
     std::vector<Pass> fwd(P.begin(), P.begin() + mi);
     if ((rc = run_passes(*plan, fwd, f, nullptr, w + 2 * half, w, w + half, s))) return rc;
@@ -711,18 +712,20 @@ int mifft_spectral_divergence(mifft_plan plan, const void* vx, const void* vy, c
     if (d == vx || d == vy || d == vz) return set_error(MIFFT_ERR_INVALID, "d must not overlap the inputs");
     const void* v[3] = {vx, vy, vz};
     const std::vector<Pass>& P = plan->exec_poisson();
-    const int mi = plan->exec_mul(), nm = plan->poisson_mul_n;
+    const int mi = plan->exec_mul(), nm = plan->exec_mul_n();
     const Pass& M = P[mi];
     const BufId D = M.src;
+    const bool split = M.kind == P_COLS_MID; // two spectra of spec_bytes: D, and the sum in the second one
+    const BufId S = split ? B_RECV : B_WS;
     char* w = (char*)(ws ? ws : plan->ws);
-    const size_t half = plan->poisson_ws_bytes / 2;
+    const size_t half = split ? plan->spec_bytes : plan->poisson_ws_bytes / 2;
     hipStream_t s = (hipStream_t)stream;
     for (int j = 0; j < 3; ++j) {
         std::vector<Pass> list(P.begin(), P.begin() + mi);
-        for (int k = 0; k < nm; ++k) { // the multiply: D -> C (the third buffer), summed over j
+        for (int k = 0; k < nm; ++k) { // the multiply: D -> S, summed over j
             Pass m = P[mi + k];
             m.src = D;
-            m.dst = B_WS;
+            m.dst = S;
             m.op = MIFFT_OP_DX + j;
             m.acc = j > 0;
             list.push_back(m);
@@ -730,7 +733,7 @@ int mifft_spectral_divergence(mifft_plan plan, const void* vx, const void* vy, c
         if ((rc = run_passes(*plan, list, v[j], nullptr, w + 2 * half, w, w + half, s))) return rc;
     }
     std::vector<Pass> inv;
-    for (size_t k = mi + nm; k < P.size(); ++k) inv.push_back(renamed(P[k], D, B_WS));
+    for (size_t k = mi + nm; k < P.size(); ++k) inv.push_back(renamed(P[k], D, S));
     return run_passes(*plan, inv, nullptr, d, w + 2 * half, w, w + half, s);
 }
 
@@ -888,7 +891,7 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
     if (!is_live(plan)) return set_error(MIFFT_ERR_BADPLAN, "handle is not a live plan");
     static const char* kn[] = {"contig", "contig_pack", "strided", "strided_unpack", "r2c_z",
                                "c2r_z",  "poisson",     "pack",    "unpack",         "copy", "poisson_x",
-                               "strided_pack", "plane", "plane_r2c", "plane_c2r", "cols"};
+                               "strided_pack", "plane", "plane_r2c", "plane_c2r", "cols", "cols_mid"};
     std::string s;
     auto add = [&](const char* tag, const Pass& q) {
         char line[768];

@@ -178,6 +178,124 @@ __device__ __forceinline__ void cols_stage(const ColsCtx<T>& x, const ColsArgs<T
     }
 }
 
+// ------------------------------------------------- spectral operators
+// The middle of a spectral operator on a split y-axis: the columns pass, the
+// multiplier, and the columns pass of the inverse, on the tile in LDS; one
+// read and one write of the spectrum for the four transforms.  The inverse
+// along x is the forward's flow graph transposed (decimation in time): it
+// takes the digit-reversed rows the forward leaves and ends in natural order,
+// and its first butterflies take what the forward's last ones hold.
+template <typename T> struct MidArgs {
+    ColsArgs<T> c; // out: results, in place or another buffer; twn is set
+    int n1, n2, A; // k1 = g + A kb; k2 = the column
+    int op, acc;   // acc: add to what out holds
+    T scale, alpha;
+};
+
+// The last forward stage, the multiplier and the first stage back.
+template <typename T, int R>
+__device__ __forceinline__ void mid_turn(const ColsCtx<T>& x, const MidArgs<T>& m, const SpectralCol<T>& col)
+{
+    using V = cx<T>;
+    const int n0 = m.c.cp.A, nb = n0 / R;
+    for (int g = x.b0; g < nb; g += x.bs) {
+        V* p = x.tile + g * R * x.P + x.p;
+        V v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = p[r * x.P];
+        Bfly<R>::fwd(v);
+        const int k0 = x.rev[g * R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            v[r] = spectral_mul<T>(m.op, k0 + r * nb, n0, col, m.scale, m.alpha, v[r]);
+            v[r].y = -v[r].y; // the inverse runs as conj(F(conj(.)))
+        }
+        Bfly<R>::fwd(v);
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[r * x.P] = v[r];
+    }
+}
+
+// A stage back: twiddles, then the butterfly.
+template <typename T, int R> __device__ __forceinline__ void mid_back(const ColsCtx<T>& x, const ColsArgs<T>& a, const ColStage& s)
+{
+    using V = cx<T>;
+    const int nb = a.cp.A / R, q = s.q;
+    for (int b = x.b0; b < nb; b += x.bs) {
+        const int g = (int)__umulhi((uint32_t)b, s.mq); // q > 1
+        const int off = b - g * q;
+        V* p = x.tile + (g * R * q + off) * x.P + x.p;
+        V v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = p[r * q * x.P];
+        const int e = off * s.tws;
+        const V* w = x.tw;
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[r] = cmul(v[r], *(w += e));
+        Bfly<R>::fwd(v);
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[r * q * x.P] = v[r];
+    }
+}
+
+// y1 back: the B values of (x, c), with the factors w_n1^{y1 g}, to global memory.
+template <typename T, int R>
+__device__ __forceinline__ void mid_store(const ColsCtx<T>& x, const MidArgs<T>& m, cx<T>* out, bool valid, int g)
+{
+    using V = cx<T>;
+    const ColsArgs<T>& a = m.c;
+    if (!valid) return;
+    V w[R];
+#pragma unroll
+    for (int r = 1; r < R; ++r) w[r] = a.twn[r * g];
+    for (int b = x.tid / x.C; b < a.cp.A; b += x.nt / x.C) {
+        const V* q = x.tile + b * x.P + x.c;
+        V v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = q[r * x.C];
+        Bfly<R>::fwd(v);
+        const uint32_t o = (uint32_t)b * a.es_out;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r > 0) v[r] = cmul(v[r], w[r]);
+            v[r].y = -v[r].y;
+            V* p = at(out, o + r * a.ys_out);
+            if (m.acc) {
+                const V old = *p;
+                v[r].x += old.x;
+                v[r].y += old.y;
+            }
+            *p = v[r];
+        }
+    }
+}
+
+// fn<R>() for the radices of a stage along x.
+template <typename T, typename F> __device__ __forceinline__ void radix_switch(int R, F&& fn)
+{
+    switch (R) {
+    case 2: fn(std::integral_constant<int, 2>{}); break;
+    case 3: fn(std::integral_constant<int, 3>{}); break;
+    case 4: fn(std::integral_constant<int, 4>{}); break;
+    case 5: fn(std::integral_constant<int, 5>{}); break;
+    case 6: fn(std::integral_constant<int, 6>{}); break;
+    case 8: fn(std::integral_constant<int, 8>{}); break;
+    default:
+        if constexpr (sizeof(T) == 4) {
+            if (R == 9)
+                fn(std::integral_constant<int, 9>{});
+            else if (R == 10)
+                fn(std::integral_constant<int, 10>{});
+            else if (R == 12)
+                fn(std::integral_constant<int, 12>{});
+            else if (R == 15)
+                fn(std::integral_constant<int, 15>{});
+            else if (R == 16)
+                fn(std::integral_constant<int, 16>{});
+        }
+    }
+}
+
 template <typename T, bool LAST>
 __device__ __forceinline__ void cols_dispatch(const ColsCtx<T>& x, const ColsArgs<T>& a, ColStage s, cx<T>* out,
                                               bool valid, cx<T> w)
@@ -185,36 +303,13 @@ __device__ __forceinline__ void cols_dispatch(const ColsCtx<T>& x, const ColsArg
     s.q = __builtin_amdgcn_readfirstlane(s.q);
     s.tws = __builtin_amdgcn_readfirstlane(s.tws);
     asm volatile("" : "+s"(s.q), "+s"(s.tws)); // as in col_dispatch
-    switch (s.R) {
-    case 2: cols_stage<T, 2, LAST>(x, a, s, out, valid, w); break;
-    case 3: cols_stage<T, 3, LAST>(x, a, s, out, valid, w); break;
-    case 4: cols_stage<T, 4, LAST>(x, a, s, out, valid, w); break;
-    case 5: cols_stage<T, 5, LAST>(x, a, s, out, valid, w); break;
-    case 6: cols_stage<T, 6, LAST>(x, a, s, out, valid, w); break;
-    case 8: cols_stage<T, 8, LAST>(x, a, s, out, valid, w); break;
-    default:
-        if constexpr (sizeof(T) == 4) {
-            if (s.R == 9)
-                cols_stage<T, 9, LAST>(x, a, s, out, valid, w);
-            else if (s.R == 10)
-                cols_stage<T, 10, LAST>(x, a, s, out, valid, w);
-            else if (s.R == 12)
-                cols_stage<T, 12, LAST>(x, a, s, out, valid, w);
-            else if (s.R == 15)
-                cols_stage<T, 15, LAST>(x, a, s, out, valid, w);
-            else if (s.R == 16)
-                cols_stage<T, 16, LAST>(x, a, s, out, valid, w);
-        }
-    }
+    radix_switch<T>(s.R, [&](auto R) { cols_stage<T, decltype(R)::value, LAST>(x, a, s, out, valid, w); });
 }
 
-template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T> a)
+// The thread's place in a tile, and the tables after the tile.
+template <typename T> __device__ __forceinline__ void cols_setup(ColsCtx<T>& x, const ColsArgs<T>& a, cx<T>* tile)
 {
-    using V = cx<T>;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    V* tile = reinterpret_cast<V*>(smem_raw);
     const int L = a.cp.A;
-    ColsCtx<T> x;
     x.tile = tile;
     x.tid = threadIdx.x;
     x.nt = blockDim.x;
@@ -222,10 +317,9 @@ template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T>
     x.P = a.B * a.C;
     x.p = x.tid % x.P;
     x.c = x.p % a.C;
-    const int y1 = x.p / a.C;
     x.b0 = x.tid / x.P;
     x.bs = x.nt / x.P;
-    V* tw = tile + L * x.P;
+    cx<T>* tw = tile + L * x.P;
     unsigned short* rev = reinterpret_cast<unsigned short*>(tw + L);
     for (int i = x.tid; i < L; i += x.nt) {
         tw[i] = a.tw[i];
@@ -233,21 +327,33 @@ template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T>
     }
     x.tw = tw;
     x.rev = rev;
-    // (group, column) of this thread in tile i; false past the last column.
-    // Consecutive workgroups run on different XCDs: each XCD takes a
-    // consecutive run of tiles, so that tiles that share cache lines share an L2.
-    auto locate = [&](int i, int& g, int& col) -> bool {
-        const int t = a.xcd ? (i & 7) * (a.ntiles >> 3) + (i >> 3) : i;
-        if (a.flat) {
-            const uint32_t f = (uint32_t)t * (uint32_t)a.C + (uint32_t)x.c;
-            g = (int)(f / (uint32_t)a.cols);
-            col = (int)(f - (uint32_t)g * (uint32_t)a.cols);
-            return g < a.groups;
-        }
-        g = t / a.tpg;
-        col = (t - g * a.tpg) * a.C + x.c;
-        return col < a.cols;
-    };
+}
+
+// (group, column) of a thread in tile i; false past the last column.
+// Consecutive workgroups run on different XCDs: each XCD takes a consecutive
+// run of tiles, so that tiles that share cache lines share an L2.
+template <typename T>
+__device__ __forceinline__ bool cols_locate(const ColsArgs<T>& a, int c, int i, int& g, int& col)
+{
+    const int t = a.xcd ? (i & 7) * (a.ntiles >> 3) + (i >> 3) : i;
+    if (a.flat) {
+        const uint32_t f = (uint32_t)t * (uint32_t)a.C + (uint32_t)c;
+        g = (int)(f / (uint32_t)a.cols);
+        col = (int)(f - (uint32_t)g * (uint32_t)a.cols);
+        return g < a.groups;
+    }
+    g = t / a.tpg;
+    col = (t - g * a.tpg) * a.C + c;
+    return col < a.cols;
+}
+
+template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T> a)
+{
+    using V = cx<T>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    ColsCtx<T> x;
+    cols_setup<T>(x, a, reinterpret_cast<V*>(smem_raw));
+    const int y1 = x.p / a.C;
     const V* ain = a.in;
     V* aout = a.out;
     if (gridDim.y > 1) {
@@ -257,7 +363,7 @@ template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T>
     int i = blockIdx.x;
     if (i >= a.ntiles) return;
     int g, col;
-    bool valid = locate(i, g, col);
+    bool valid = cols_locate(a, x.c, i, g, col);
     V pre[cols_slots<T>()];
     cols_load<T>(x, a, ain + (valid ? (long long)g * a.gs_in + col : 0), valid, pre);
     __syncthreads();
@@ -270,7 +376,7 @@ template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T>
         const int next = i + (int)gridDim.x;
         bool nvalid = false;
         if (next < a.ntiles) { // the next tile's loads, in flight during this one's stages
-            nvalid = locate(next, g, col);
+            nvalid = cols_locate(a, x.c, next, g, col);
             cols_load<T>(x, a, ain + (nvalid ? (long long)g * a.gs_in + col : 0), nvalid, pre);
         }
         __syncthreads();
@@ -283,6 +389,52 @@ template <typename T> __global__ __launch_bounds__(1024) void k_cols(ColsArgs<T>
         __syncthreads(); // the next tile's rows overwrite this one's
         i = next;
         valid = nvalid;
+    }
+}
+
+template <typename T> __global__ __launch_bounds__(1024) void k_cols_mid(MidArgs<T> m)
+{
+    using V = cx<T>;
+    const ColsArgs<T>& a = m.c;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    ColsCtx<T> x;
+    cols_setup<T>(x, a, reinterpret_cast<V*>(smem_raw));
+    const int kb = x.p / a.C;
+    __syncthreads();
+    const V none{T(1), T(0)};
+    // (the next tile's loads held through both transforms would not fit 128 registers)
+    for (int i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
+        int g, col;
+        const bool valid = cols_locate(a, x.c, i, g, col);
+        asm volatile("" : "+v"(x.tid), "+v"(x.p), "+v"(x.c), "+v"(x.b0)); // as in k_strided
+        {
+            V pre[cols_slots<T>()];
+            cols_load<T>(x, a, a.in + (valid ? (long long)g * a.gs_in + col : 0), valid, pre);
+            cols_first<T>(x, a, pre);
+        }
+        const SpectralCol<T> sc = spectral_col<T>(m.op, g + m.A * kb, col, m.n1, m.n2, m.scale);
+        __syncthreads();
+        for (int k = 0; k + 1 < a.cp.n; ++k) {
+            cols_dispatch<T, false>(x, a, a.cp.s[k], nullptr, valid, none);
+            __syncthreads();
+        }
+        radix_switch<T>(a.cp.s[a.cp.n - 1].R, [&](auto R) { mid_turn<T, decltype(R)::value>(x, m, sc); });
+        __syncthreads();
+        for (int k = a.cp.n - 2; k >= 0; --k) {
+            const ColStage s = a.cp.s[k];
+            radix_switch<T>(s.R, [&](auto R) { mid_back<T, decltype(R)::value>(x, a, s); });
+            __syncthreads();
+        }
+        V* out = a.out + (valid ? (long long)g * a.gs_out + col : 0);
+        switch (a.B) {
+        case 2: mid_store<T, 2>(x, m, out, valid, g); break;
+        case 3: mid_store<T, 3>(x, m, out, valid, g); break;
+        case 4: mid_store<T, 4>(x, m, out, valid, g); break;
+        case 5: mid_store<T, 5>(x, m, out, valid, g); break;
+        case 6: mid_store<T, 6>(x, m, out, valid, g); break;
+        default: mid_store<T, 8>(x, m, out, valid, g); break;
+        }
+        if (i + (int)gridDim.x < a.ntiles) __syncthreads();
     }
 }
 

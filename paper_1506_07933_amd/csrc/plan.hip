@@ -503,8 +503,10 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         hipLaunchKernelGGL(fn, dim3(gx, ng), dim3(p.block), p.shmem, s, a);
         break;
     }
-    case P_COLS: {
-        ColsArgs<T> a{};
+    case P_COLS:
+    case P_COLS_MID: {
+        MidArgs<T> m{};
+        ColsArgs<T>& a = m.c;
         a.in = (const V*)src;
         a.out = (V*)dst;
         for (int i = 0; i < ng && ng > 1; ++i) {
@@ -530,7 +532,18 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         a.nt_out = p.nt_out;
         a.xcd = p.ntiles % 8 == 0 && !getenv("MIFFT_NOXCD");
         a.cp = *p.cp;
-        ensure_lds(cols_kernel(sizeof(T) == 8), p.shmem);
+        const bool mid = p.kind == P_COLS_MID;
+        ensure_lds(cols_kernel(sizeof(T) == 8, mid), p.shmem);
+        if (mid) {
+            m.n1 = p.n1;
+            m.n2 = p.nz;
+            m.A = p.groups;
+            m.op = p.op;
+            m.acc = p.acc;
+            m.scale = (T)p.scale;
+            m.alpha = (T)p.alpha;
+            return launch_cols_mid(m, dim3(p.grid), p.block, p.shmem, s);
+        }
         unsigned gx = p.grid;
         if (ng > 1 && (int)p.grid < p.ntiles) gx = std::max(1u, (p.grid + (unsigned)ng - 1) / (unsigned)ng);
         return launch_cols(a, dim3(gx, ng), p.block, p.shmem, s);
@@ -1184,7 +1197,8 @@ Extent pass_extent(const Pass& p, size_t esz)
         e.out = oo + x * p.os_o + b * p.os_b + r * p.os_i + p.L + (p.kind == P_PLANE_R2C);
         break;
     }
-    case P_COLS: {
+    case P_COLS:
+    case P_COLS_MID: {
         const long long g = p.groups - 1, x = p.cp->A - 1, y = p.nb - 1;
         e.in = oi + g * p.gs_in + x * p.es_in + y * p.ys_in + p.cols;
         e.out = oo + g * p.gs_out + x * p.es_out + y * p.ys_out + p.cols;
@@ -1258,7 +1272,9 @@ int validate_extents(const Plan& plan)
             const Pass& p = (*l.v)[k];
             const Extent e = pass_extent(p, plan.esz);
             const bool ip = l.v == &plan.plane_fwd_ip || l.v == &plan.plane_inv_ip;
+            const bool chain = l.v == &plan.plane_poisson && plan.spec_bytes; // one spectrum, in both halves
             auto cap = [&](BufId b) -> long long {
+                if (chain && b == B_SEND) return std::min(2 * pw, (long long)(plan.spec_bytes / esz));
                 return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? (ip ? own : ws) : (b == B_SEND || b == B_RECV) ? pw : 0;
             };
             if ((p.src != B_NONE && e.in > cap(p.src)) || (p.dst != B_NONE && e.out > cap(p.dst)))
@@ -1803,19 +1819,12 @@ static const void* plane_fn(int prec, const Pass& p)
 }
 
 // Resident grid over p.ntiles, balanced as in strided_grid (a plane pass reads
-// a workgroup's next tile while its last one is transformed).
-static void resident_grid(const Plan& plan, Pass& p, const void* fn)
+// a workgroup's next tile while its last one is transformed).  The kernels
+// take 65 to 128 registers, so sixteen wavefronts share a CU.
+static void resident_grid(const Plan& plan, Pass& p)
 {
-    int per_cu = 0;
-    if (!plan.plan_only) {
-        ensure_lds(fn, p.shmem);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)p.block, p.shmem) != hipSuccess) {
-            (void)hipGetLastError();
-            per_cu = 0;
-        }
-    }
-    if (per_cu <= 0) per_cu = (int)std::max<size_t>(1, std::min(kLdsMax / p.shmem, (size_t)(2048 / p.block)));
-    const long long cap = (long long)plan.cus * per_cu;
+    const size_t per_cu = std::max<size_t>(1, std::min(kLdsMax / p.shmem, (size_t)(1024 / p.block)));
+    const long long cap = (long long)plan.cus * (long long)per_cu;
     p.grid = (unsigned)p.ntiles;
     if (p.ntiles > cap) {
         const long long rounds = (p.ntiles + cap - 1) / cap;
@@ -1858,7 +1867,7 @@ static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool
     p.block = (unsigned)(waves * 64);
     p.shmem = lds;
     p.ntiles = tiles;
-    resident_grid(plan, p, plane_fn(plan.prec, p));
+    resident_grid(plan, p);
     *ok = true;
     return MIFFT_OK;
 }
@@ -1937,12 +1946,17 @@ static int cols_threads(const Plan& plan, int B, int C, long long tiles)
 // 82 -> 61; the plane alone on its CU: 256^3 FP32 C2C 152 -> 115, R2C 95 -> 72;
 // both alone, 128-byte rows: 256^3 FP64 R2C 180 -> 137, C2R 152 -> 137; both
 // alone, 64-byte rows: 256^3 FP64 C2C 297 -> 330, 1024 x 64 x 512 FP32 323 -> 328;
-// 64-byte rows that straddle lines: 500 x 200 x 180 FP32 210 -> 225.
-static bool choose_split(const Plan& plan, int L, int nc, Split* s)
+// 64-byte rows that straddle lines: 500 x 200 x 180 FP32 210 -> 225.  Spectral
+// solves (five passes against three; B, C): 256^3 FP32 157 us, 2,16 127, 4,8 137;
+// FP64 251, 4,4 210, 4,8 227; 128^3 FP64 61, 4,8 46, 2,8 50.
+// `inner`: both of the second pass's sides are internal (rows padded to whole
+// lines, tiles of one group: the last one may be nearly empty).
+static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
 {
     int fb = 0, fc = 0; // MIFFT_SPLIT=B,C: that split where it fits (comparison, tests)
     if (const char* e = getenv("MIFFT_SPLIT")) sscanf(e, "%d,%d", &fb, &fc);
-    double best = fb ? 1e9 : 2.35;
+    double best = fb ? 1e9 : inner ? 2.4 : 2.35;
+    size_t best_cl = 0;
     bool found = false;
     for (int B : {2, 3, 4, 5, 6, 8}) {
         if (plan.n1 % B || plan.n1 / B < 2 || (fb && B != fb)) continue;
@@ -1952,10 +1966,12 @@ static bool choose_split(const Plan& plan, int L, int nc, Split* s)
             const size_t cl = cols_lds(plan, B, C);
             if ((fc ? C != fc : row < 64 || row > 256) || pl > kLdsMax || cl > kLdsMax || !cols_threads(plan, B, C, (long long)plan.n1 / B * nc / C))
                 continue;
-            const double rows = row >= 128 ? 1.0 : (size_t)nc * plan.esz % 128 == 0 ? 1.1 : 1.25;
+            double rows = row >= 128 ? 1.0 : inner ? 1.2 : (size_t)nc * plan.esz % 128 == 0 ? 1.1 : 1.25;
+            if (inner) rows *= (double)((nc + C - 1) / C * C) / nc;
             const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (2 * cl > kLdsMax ? 1.2 : 1.0) * rows;
-            if (cost < best) {
+            if (cost < best || (cost == best && cl > best_cl)) { // the larger tile: less set-up
                 best = cost;
+                best_cl = cl;
                 *s = Split{plan.n1 / B, B, C};
                 found = true;
             }
@@ -1979,7 +1995,7 @@ static int build_split(Plan& plan)
     if (plan.nd || n0 < 2 || n1 < 4 || plan.n2 < 2) return MIFFT_OK;
     Split sp;
     const int L = real ? plan.n2 / 2 : plan.n2;
-    if (L < 2 || !choose_split(plan, L, nc, &sp)) return MIFFT_OK;
+    if (L < 2 || !choose_split(plan, L, nc, false, &sp)) return MIFFT_OK;
     const int A = sp.A, B = sp.B;
     // Without the workspace's large strides three passes are at their best:
     // 128^3 C2C FP32 24.3 us against 27.4, 128 x 128 x 64 FP64 24.3 against 26.8;
@@ -2069,7 +2085,7 @@ static int build_split(Plan& plan)
         const size_t out_bytes = (size_t)n0 * plane * plan.esz;
         a.nt_out = c2r && out_bytes >= ((size_t)128 << 20);
         c.nt_out = out_bytes > ((size_t)256 << 20);
-        resident_grid(plan, c, cols_kernel(plan.prec == MIFFT_FP64));
+        resident_grid(plan, c);
         (dir ? plan.plane_inv : plan.plane_fwd) = c2r ? std::vector<Pass>{c, a} : std::vector<Pass>{a, c};
         if (plan.plane_oop) {
             a.dst = c.src = B_WS;
@@ -2083,12 +2099,73 @@ static int build_split(Plan& plan)
     return MIFFT_OK;
 }
 
+// The split spectral chain: plane pass (IN -> D), columns there and back with
+// the multiplier (D in place), plane pass (D -> OUT); D[ka][x][y1][k2] with rows
+// of whole 128-byte lines at the start of the workspace (whose halves, sized
+// for the one-axis chain, hold it).
+static int build_split_spectral(Plan& plan)
+{
+    const int n0 = plan.n0, n1 = plan.n1, M = plan.n2 / 2, nc = M + 1;
+    if (plan.nd || plan.kind != MIFFT_R2C || n0 < 2 || n1 < 4 || M < 2 || plan.poisson_mul < 0) return MIFFT_OK;
+    Split sp;
+    if (!choose_split(plan, M, nc, true, &sp)) return MIFFT_OK;
+    const int A = sp.A, B = sp.B, line = (int)(128 / plan.esz), pitch = (nc + line - 1) / line * line;
+    const size_t bytes = (size_t)n0 * n1 * pitch * plan.esz;
+    // gradient and divergence hold two spectra in the three halves
+    if (bytes > plan.poisson_ws_bytes || 2 * bytes > plan.spectral_ws_bytes || bytes >= (1ull << 32)) return MIFFT_OK;
+    Pass z, a, c, b;
+    int rc = make_real_z(plan, z, P_R2C, (long long)n0 * n1);
+    if (rc) return rc;
+    bool ok = false;
+    if ((rc = make_plane(plan, a, z, A, n0 * B, true, &ok)) || !ok) return rc;
+    z.kind = P_C2R;
+    if ((rc = make_plane(plan, b, z, A, n0 * B, true, &ok)) || !ok) return rc;
+    void* twn = nullptr;
+    if ((rc = get_twiddles(plan, n1, &twn)) || (rc = get_twiddles(plan, n0, (void**)&c.tw))) return rc;
+    if (!(c.cp = col_plan(plan, n0))) return MIFFT_OK;
+    a.src = B_IN;
+    a.dst = c.src = c.dst = b.src = B_SEND;
+    b.dst = B_OUT;
+    a.nb = b.nb = c.nb = B;
+    a.twn = c.twn = twn;
+    a.split_tw = c.split_tw = 1;
+    a.is_o = b.os_o = (long long)n1 * M;
+    a.is_b = b.os_b = M;
+    a.is_i = b.os_i = (long long)B * M;
+    a.os_o = b.is_o = (long long)B * pitch;
+    a.os_b = b.is_b = pitch;
+    a.os_i = b.is_i = (long long)n0 * B * pitch;
+    b.nt_out = (size_t)n0 * n1 * M * plan.esz >= ((size_t)128 << 20);
+    c.kind = P_COLS_MID;
+    c.L = n0;
+    c.tag = 2;
+    c.split_C = sp.C;
+    c.cols = nc;
+    c.groups = A;
+    c.gs_in = c.gs_out = a.os_i;
+    c.es_in = c.es_out = a.os_o;
+    c.ys_in = c.ys_out = pitch;
+    c.n1 = n1;
+    c.nz = plan.n2;
+    c.scale = 1.0 / ((double)n0 * n1 * plan.n2);
+    c.tpg = (nc + sp.C - 1) / sp.C;
+    c.ntiles = A * c.tpg;
+    c.shmem = cols_lds(plan, B, sp.C);
+    c.block = (unsigned)cols_threads(plan, B, sp.C, c.ntiles);
+    resident_grid(plan, c);
+    plan.plane_poisson = {a, c, b};
+    plan.plane_mul = 1;
+    plan.spec_bytes = (bytes + 255) / 256 * 256;
+    return MIFFT_OK;
+}
+
 int build_planes(Plan& plan)
 {
     plan.plane_fwd.clear();
     plan.plane_inv.clear();
     plan.plane_poisson.clear();
     plan.plane_mul = -1;
+    plan.spec_bytes = 0;
     plan.plane_oop = false;
     plan.plane_fwd_ip.clear();
     plan.plane_inv_ip.clear();
@@ -2111,7 +2188,9 @@ int build_planes(Plan& plan)
     }
     if ((rc = build_split(plan))) return rc;
     const char* unfused = getenv("MIFFT_POISSON_UNFUSED");
-    if (po.size() >= 5 && plan.poisson_mul_n == 1 && !(unfused && atoi(unfused) != 0)) {
+    const bool general = (unfused && atoi(unfused) != 0) || getenv("MIFFT_POISSON_NYQ");
+    if (getenv("MIFFT_SPLIT") && !general && (rc = build_split_spectral(plan))) return rc;
+    if (plan.plane_poisson.empty() && po.size() >= 5 && plan.poisson_mul_n == 1 && !(unfused && atoi(unfused) != 0)) {
         bool f2 = false;
         if ((rc = fuse_plane(plan, po, 0, &fused))) return rc;
         const int mul = plan.poisson_mul - (fused ? 1 : 0);
@@ -2121,6 +2200,7 @@ int build_planes(Plan& plan)
             plan.plane_mul = mul;
         }
     }
+    if (plan.plane_poisson.empty() && !general && (rc = build_split_spectral(plan))) return rc;
     return validate_extents(plan);
 }
 

@@ -33,7 +33,8 @@ enum PassKind {
     P_PLANE,          // z- and y-axis of a plane in LDS (plane.hpp)
     P_PLANE_R2C,
     P_PLANE_C2R,
-    P_COLS            // y1 and x of a split y-axis (cols.hpp)
+    P_COLS,           // y1 and x of a split y-axis (cols.hpp)
+    P_COLS_MID        // those of a spectral operator: forward, multiply, inverse
 };
 
 // Which caller buffer a pass reads or writes; resolved at execute time.
@@ -130,6 +131,9 @@ public:
     // and y fused into one pass; empty where the lists above run as they are.
     std::vector<Pass> plane_fwd, plane_inv, plane_poisson;
     int plane_mul = -1; // index of the multiply pass in plane_poisson
+    // split spectral chain: its spectra (of spec_bytes, from the start of the
+    // workspace on) take the place of the halves; 0: not split
+    size_t spec_bytes = 0;
     // plane_fwd / plane_inv of a C2C plan run out of place only; in place the
     // same passes go through the plan's own workspace (these lists), or, in
     // calls that bring their own (of ws_bytes, which is 0), fwd / inv run
@@ -138,6 +142,7 @@ public:
     const std::vector<Pass>& exec_fwd() const { return plane_fwd.empty() ? fwd : plane_fwd; }
     const std::vector<Pass>& exec_inv() const { return plane_inv.empty() ? inv : plane_inv; }
     const std::vector<Pass>& exec_poisson() const { return plane_poisson.empty() ? poisson : plane_poisson; }
+    int exec_mul_n() const { return plane_poisson.empty() ? poisson_mul_n : 1; }
     int exec_mul() const { return plane_poisson.empty() ? poisson_mul : plane_mul; }
     int blocked = 0; // block width (columns) of the blocked intermediates, 0: not used
     // pencil stages
@@ -252,7 +257,9 @@ int build_nd(Plan& plan, unsigned flags);
 // Fuse the z- and y-passes of a built plan's lists into plane passes (untuned plans).
 int build_planes(Plan& plan);
 
-const void* cols_kernel(bool fp64);
+const void* cols_kernel(bool fp64, bool mid = false);
+hipError_t launch_cols_mid(const MidArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
+hipError_t launch_cols_mid(const MidArgs<double>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
 hipError_t launch_cols(const ColsArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
 hipError_t launch_cols(const ColsArgs<double>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
 

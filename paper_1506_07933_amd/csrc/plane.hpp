@@ -411,10 +411,14 @@ template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
         constexpr int R = Z::f.r[I], TPL = Z::TPL;
         constexpr int NBF = L / R, NB = (NBF + TPL - 1) / TPL;
         constexpr bool EXACT = NBF % TPL == 0, FIRST = I == 0, LAST = I + 1 == Z::f.n;
+        // A last stage that stores to global memory takes adjacent butterflies
+        // per thread, so that it stores 16 bytes at a time.
+        constexpr bool PAIR = LAST && !FIRST && Ctx::kPairOut && EXACT && NB == 2 && NBF % 2 == 0 && sizeof(T) == 4;
+        auto bfly_of = [&](int i) { return PAIR ? 2 * c.t + i : c.t + i * TPL; };
         V v[NB][R];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int j = c.t + i * TPL;
+            const int j = bfly_of(i);
             if (EXACT || j < NBF) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -429,7 +433,7 @@ template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
         if constexpr (!FIRST || Ctx::kFirstFromRow) wave_sync();
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int j = c.t + i * TPL;
+            const int j = bfly_of(i);
             if (EXACT || j < NBF) {
                 const int a = j / Ns, k = j - a * Ns;
                 if constexpr (Ns > 1) {
@@ -440,7 +444,9 @@ template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
                 Bfly<R>::fwd(v[i]);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    if constexpr (LAST)
+                    if constexpr (PAIR) {
+                        if (i == 1) c.final_pair(j - 1 + r * NBF, v[0][r], v[1][r]);
+                    } else if constexpr (LAST)
                         c.final_put(j + r * NBF, v[i][r]);
                     else
                         c.row[pad_write<Z::SH, Ns, R>(a, k, r)] = v[i][r];
@@ -459,7 +465,7 @@ template <typename T, int L, int I, int Ns, typename Ctx> struct ZStage {
 template <typename T, int L> struct ZForward {
     using V = cx<T>;
     using Z = ZShape<T, L>;
-    static constexpr bool kFirstFromRow = false;
+    static constexpr bool kFirstFromRow = false, kPairOut = false;
     V* row;
     const V* twd; // twiddle table staged in LDS
     int t;
@@ -488,7 +494,7 @@ template <typename T, int L> struct ZForward {
 // stage reads them pre-processed, the last stage writes pairs of reals.
 template <typename T, int L> struct ZInverseReal {
     using V = cx<T>;
-    static constexpr bool kFirstFromRow = true;
+    static constexpr bool kFirstFromRow = true, kPairOut = true;
     V* row;
     const V* twd;
     const V* tw2; // exp(-2 pi i k / 2L)
@@ -509,6 +515,16 @@ template <typename T, int L> struct ZInverseReal {
         return cconj(z);
     }
     __device__ __forceinline__ void first_done() const {}
+    // elements idx (even) and idx + 1: rows start at multiples of L (even) pairs
+    __device__ __forceinline__ void final_pair(int idx, V a, V b)
+    {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const f4 v{(float)a.x, (float)-a.y, (float)b.x, (float)-b.y};
+        if (nt)
+            __builtin_nontemporal_store(v, reinterpret_cast<f4*>(out + idx));
+        else
+            *reinterpret_cast<f4*>(out + idx) = v;
+    }
     __device__ __forceinline__ void final_put(int idx, V v)
     {
         if (nt)

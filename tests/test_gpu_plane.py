@@ -159,3 +159,32 @@ def test_grouped_split_planes(monkeypatch):
     for d, o in zip(data, outs):
         assert rel_l2(o.cpu().numpy(), oracle.fft3d_c2c(d.astype(np.complex128), -1)) <= TOL["fp32"]
     b.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("split,shape", [("2,8", (6, 8, 60)), ("3,16", (125, 12, 30)), ("4,8", (16, 256, 128)),
+                                         ("5,8", (2, 20, 64)), ("6,8", (81, 24, 60)), ("8,4", (10, 32, 50))])
+def test_split_spectral_operators(monkeypatch, split, shape, prec):
+    """Every operator, gradient and divergence on a split y-axis, one to four
+    stages along x; with a caller workspace too; inputs are kept."""
+    from paper_1506_07933_amd import Plan
+    monkeypatch.setenv("MIFFT_SPLIT", split)
+    rd = np.float32 if prec == "fp32" else np.float64
+    f = synth.normal_real(shape, rd, seed=5)
+    f = (f - f.mean(dtype=np.float64)).astype(rd)
+    f64 = f.astype(np.float64)
+    p = Plan(shape, "r2c", prec)
+    assert [line.split()[1] for line in _plane_lines(p, "poisson")] == ["kind=plane_r2c", "kind=cols_mid", "kind=plane_c2r"]
+    fd = torch.from_numpy(f).cuda()
+    for op in range(6):
+        ref = oracle.spectral_apply(f64, op, 1.5)
+        assert rel_l2(p.spectral(op, fd, alpha=1.5).cpu().numpy(), ref) <= TOL[prec], op
+    g = p.gradient(fd)
+    for j, r in enumerate(oracle.gradient(f64)):
+        assert rel_l2(g[j].cpu().numpy(), r) <= TOL[prec]
+        assert torch.equal(g[j], p.spectral(oracle.OP_DX + j, fd))
+    v = [synth.normal_real(shape, rd, seed=20 + j) for j in range(3)]
+    d = p.divergence([torch.from_numpy(u).cuda() for u in v])
+    assert rel_l2(d.cpu().numpy(), oracle.divergence(*[u.astype(np.float64) for u in v])) <= TOL[prec]
+    np.testing.assert_array_equal(fd.cpu().numpy(), f)
+    p.close()

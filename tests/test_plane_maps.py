@@ -142,3 +142,35 @@ def test_switches_keep_the_one_axis_passes(monkeypatch):
     lists, _ = _lists((64, 64, 64), 1, 0)
     assert [p["kind"] for p in lists["plane_forward"]] == ["plane_r2c", "strided"]
     assert [p["kind"] for p in lists["plane_poisson"]] == ["plane_r2c", "poisson_x", "plane_c2r"]
+
+
+@pytest.mark.parametrize("split,shape", [("2,8", (6, 8, 60)), ("3,16", (5, 12, 64)), ("4,8", (4, 256, 128)),
+                                         ("5,8", (3, 20, 40)), ("8,8", (5, 32, 36))])
+def test_split_spectral_maps(monkeypatch, split, shape):
+    """plane pass, columns there and back with a multiplier per (k0, k1, k2),
+    plane pass: the multiplier sees the frequencies it should."""
+    monkeypatch.setenv("MIFFT_SPLIT", split)
+    n0, n1, n2 = shape
+    lists, _ = _lists(shape, 1, 1)
+    po = lists["plane_poisson"]
+    assert [p["kind"] for p in po] == ["plane_r2c", "cols_mid", "plane_c2r"]
+    a, c, b = po
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal(shape)
+    m = rng.standard_normal((n0, n1, n2 // 2 + 1))
+    m[..., 0] = m[..., -1] = 0.5  # (real data: keep the ends Hermitian)
+    flat = x.reshape(-1, 2) @ [1, 1j]
+    D = np.zeros(c["groups"] * c["gs"][0], complex)
+    _plane(a, flat, D, n1)
+    L, B, A = c["rows"], c["nb"], c["groups"]
+    for g in range(A):
+        idx = np.array([[g * c["gs"][0] + i * c["es"][0] + y * c["ys"][0] for y in range(B)] for i in range(L)])
+        idx = idx[:, :, None] + np.arange(c["cols"])
+        v = _dft(_dft(D[idx], 1, 1), 1, 0) * m[:, g + A * np.arange(B), :]
+        v = _dft(_dft(v, -1, 1), -1, 0) * np.exp(2j * np.pi * np.arange(B) * g / n1)[None, :, None]
+        D[idx] = v
+    out = np.zeros(x.size // 2, complex)
+    _plane(b, D, out, n1)
+    full = np.fft.irfftn(np.fft.rfftn(x) * m, s=shape, axes=(0, 1, 2)) * x.size
+    want = full.reshape(-1, 2) @ [1, 1j]
+    assert np.linalg.norm(out - want) <= 1e-12 * np.linalg.norm(want)
