@@ -26,7 +26,6 @@ hipError_t mifft_batch_launch_float(const void*, unsigned, size_t, int*, int, hi
 hipError_t mifft_batch_launch_double(const void*, unsigned, size_t, int*, int, hipStream_t);
 int mifft_batch_blocks_per_cu_float(size_t);
 int mifft_batch_blocks_per_cu_double(size_t);
-int mifft_plan_create(mifft_plan*, int, int, int, int, int, unsigned);
 int mifft_execute_forward(mifft_plan, const void*, void*, void*);
 int mifft_plan_destroy(mifft_plan);
 }
@@ -418,7 +417,10 @@ int batch_create(mifft_batch* out, int count, const int* dims, int kind, int pre
             std::vector<int> key(dims + 3 * t, dims + 3 * t + 3);
             if (b->plans.count(key)) continue;
             mifft_plan p = nullptr;
-            int rc = mifft_plan_create(&p, key[0], key[1], key[2], MIFFT_C2C, prec, flags & MIFFT_TUNE);
+            int copies = 0;
+            for (int u = 0; u < count; ++u) copies += std::equal(key.begin(), key.end(), dims + 3 * u);
+            int rc = plan_create(&p, key[0], key[1], key[2], MIFFT_C2C, prec, flags & MIFFT_TUNE,
+                                 std::min(copies, kMaxGroup));
             if (rc) {
                 delete b;
                 return rc;

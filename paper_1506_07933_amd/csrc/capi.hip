@@ -108,6 +108,13 @@ static int create_lanes(Plan& p);
 
 int mifft_plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int prec, unsigned flags)
 {
+    return plan_create(out, n0, n1, n2, kind, prec, flags, 1);
+}
+
+} // extern "C"
+
+int mifft::plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int prec, unsigned flags, int copies)
+{
     clear_error();
     if (!out) return set_error(MIFFT_ERR_INVALID, "out is NULL");
     int rc = validate_dims(n0, n1, n2, kind, prec);
@@ -124,6 +131,7 @@ int mifft_plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int pre
     p->n2 = n2;
     p->kind = kind;
     p->prec = prec;
+    p->copies = copies;
     p->device = dev;
     if (!plan_only) {
         int cus = 0;
@@ -160,6 +168,8 @@ int mifft_plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int pre
     }
     return finish_plan(p, out);
 }
+
+extern "C" {
 
 int mifft_plan_create_nd(mifft_plan* out, int rank, const int* dims, int kind, int prec, unsigned flags)
 {

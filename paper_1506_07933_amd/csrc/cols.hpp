@@ -24,6 +24,16 @@
 
 namespace mifft {
 
+// Rows of B C elements that fill the banks a whole number of times put the
+// narrow column runs (at most 64 bytes) that the y1 steps take from several
+// rows on the same banks: four spare elements per row move each on (FP32, 128 x
+// 256 x 256 C2C 61.4 -> 57.5 us; FP64, whose runs fill more banks, gained nothing:
+// 256^3 Poisson 209 -> 212).
+constexpr int cols_pitch(int B, int C, int esz)
+{
+    return B * C + (esz == 8 && B * C % 32 == 0 && C <= 8 ? 4 : 0);
+}
+
 template <typename T> struct ColsArgs {
     const cx<T>* in;
     cx<T>* out;
@@ -32,6 +42,7 @@ template <typename T> struct ColsArgs {
     const cx<T>* twn;  // length n1: results times w_n1^{y1 g} (null: not)
     int ntiles, groups, cols;
     int B, C;
+    int pitch;         // of the tile's rows in LDS (cols_pitch)
     int flat;          // tiles over the flattened (group, column) index, else C columns of one group
     int tpg;           // tiles per group (not flat)
     // element x, y1 of column (g, c) at g gs + x es + y1 ys + c on each side
@@ -49,7 +60,7 @@ template <typename T> struct ColsCtx {
     const unsigned short* rev;
     int tid, nt;       // threads: a multiple of B C
     int p, c;          // this thread's place in a row of B C, and its column
-    int P, C;
+    int P, C, pitch;
     int b0, bs;        // first butterfly and step along x
 };
 
@@ -97,7 +108,7 @@ __device__ __forceinline__ void cols_first(const ColsCtx<T>& x, const ColsArgs<T
                 v[r].y *= a.sgn;
             }
             Bfly<R>::fwd(v);
-            V* q = x.tile + b * x.P + x.c;
+            V* q = x.tile + b * x.pitch + x.c;
 #pragma unroll
             for (int r = 0; r < R; ++r) q[r * x.C] = v[r];
         }
@@ -143,10 +154,10 @@ __device__ __forceinline__ void cols_stage(const ColsCtx<T>& x, const ColsArgs<T
         int g = b;
         if (q > 1) g = (int)__umulhi((uint32_t)b, s.mq);
         const int off = b - g * q;
-        V* p = x.tile + (g * R * q + off) * x.P + x.p;
+        V* p = x.tile + (g * R * q + off) * x.pitch + x.p;
         V v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = p[r * q * x.P];
+        for (int r = 0; r < R; ++r) v[r] = p[r * q * x.pitch];
         Bfly<R>::fwd(v);
         if constexpr (LAST) {
             const int k0 = x.rev[g * R];
@@ -173,7 +184,7 @@ __device__ __forceinline__ void cols_stage(const ColsCtx<T>& x, const ColsArgs<T
 #pragma unroll
             for (int r = 1; r < R; ++r) v[r] = cmul(v[r], *(w2 += e));
 #pragma unroll
-            for (int r = 0; r < R; ++r) p[r * q * x.P] = v[r];
+            for (int r = 0; r < R; ++r) p[r * q * x.pitch] = v[r];
         }
     }
 }
@@ -199,10 +210,10 @@ __device__ __forceinline__ void mid_turn(const ColsCtx<T>& x, const MidArgs<T>& 
     using V = cx<T>;
     const int n0 = m.c.cp.A, nb = n0 / R;
     for (int g = x.b0; g < nb; g += x.bs) {
-        V* p = x.tile + g * R * x.P + x.p;
+        V* p = x.tile + g * R * x.pitch + x.p;
         V v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = p[r * x.P];
+        for (int r = 0; r < R; ++r) v[r] = p[r * x.pitch];
         Bfly<R>::fwd(v);
         const int k0 = x.rev[g * R];
 #pragma unroll
@@ -212,7 +223,7 @@ __device__ __forceinline__ void mid_turn(const ColsCtx<T>& x, const MidArgs<T>& 
         }
         Bfly<R>::fwd(v);
 #pragma unroll
-        for (int r = 0; r < R; ++r) p[r * x.P] = v[r];
+        for (int r = 0; r < R; ++r) p[r * x.pitch] = v[r];
     }
 }
 
@@ -224,17 +235,17 @@ template <typename T, int R> __device__ __forceinline__ void mid_back(const Cols
     for (int b = x.b0; b < nb; b += x.bs) {
         const int g = (int)__umulhi((uint32_t)b, s.mq); // q > 1
         const int off = b - g * q;
-        V* p = x.tile + (g * R * q + off) * x.P + x.p;
+        V* p = x.tile + (g * R * q + off) * x.pitch + x.p;
         V v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = p[r * q * x.P];
+        for (int r = 0; r < R; ++r) v[r] = p[r * q * x.pitch];
         const int e = off * s.tws;
         const V* w = x.tw;
 #pragma unroll
         for (int r = 1; r < R; ++r) v[r] = cmul(v[r], *(w += e));
         Bfly<R>::fwd(v);
 #pragma unroll
-        for (int r = 0; r < R; ++r) p[r * q * x.P] = v[r];
+        for (int r = 0; r < R; ++r) p[r * q * x.pitch] = v[r];
     }
 }
 
@@ -249,7 +260,7 @@ __device__ __forceinline__ void mid_store(const ColsCtx<T>& x, const MidArgs<T>&
 #pragma unroll
     for (int r = 1; r < R; ++r) w[r] = a.twn[r * g];
     for (int b = x.tid / x.C; b < a.cp.A; b += x.nt / x.C) {
-        const V* q = x.tile + b * x.P + x.c;
+        const V* q = x.tile + b * x.pitch + x.c;
         V v[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = q[r * x.C];
@@ -315,11 +326,12 @@ template <typename T> __device__ __forceinline__ void cols_setup(ColsCtx<T>& x, 
     x.nt = blockDim.x;
     x.C = a.C;
     x.P = a.B * a.C;
+    x.pitch = a.pitch;
     x.p = x.tid % x.P;
     x.c = x.p % a.C;
     x.b0 = x.tid / x.P;
     x.bs = x.nt / x.P;
-    cx<T>* tw = tile + L * x.P;
+    cx<T>* tw = tile + L * x.pitch;
     unsigned short* rev = reinterpret_cast<unsigned short*>(tw + L);
     for (int i = x.tid; i < L; i += x.nt) {
         tw[i] = a.tw[i];

@@ -353,6 +353,9 @@ void strided_grid(const Plan& plan, Pass& p)
     }
 }
 
+static void plane_launch(const Pass& p, int ng, unsigned* grid, unsigned* block);
+static unsigned cols_grid(const Pass& p, int ng);
+
 // ng > 1 (contiguous and strided passes): one launch over ng transforms of
 // the same shape, member i reading gsrc[i] and writing gdst[i] (blockIdx.y).
 template <typename T>
@@ -485,6 +488,7 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         a.tw2 = (const V*)p.tw2;
         a.twy = (const V*)p.twy;
         a.ntiles = p.ntiles;
+        a.ng = ng;
         a.nb = p.nb;
         a.twn = (const V*)p.twn;
         a.is_x = p.is_o;
@@ -498,9 +502,9 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         a.cp = *p.cp;
         auto fn = p.kind == P_PLANE ? v.plane : p.kind == P_PLANE_R2C ? v.plane_r2c : v.plane_c2r;
         ensure_lds(reinterpret_cast<const void*>(fn), p.shmem);
-        unsigned gx = p.grid;
-        if (ng > 1 && (int)p.grid < p.ntiles) gx = std::max(1u, (p.grid + (unsigned)ng - 1) / (unsigned)ng);
-        hipLaunchKernelGGL(fn, dim3(gx, ng), dim3(p.block), p.shmem, s, a);
+        unsigned gx = p.grid, block = p.block;
+        if (ng > 1) plane_launch(p, ng, &gx, &block);
+        hipLaunchKernelGGL(fn, dim3(gx), dim3(block), p.shmem, s, a);
         break;
     }
     case P_COLS:
@@ -520,6 +524,7 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         a.cols = p.cols;
         a.B = p.nb;
         a.C = p.split_C;
+        a.pitch = cols_pitch(p.nb, p.split_C, (int)sizeof(V));
         a.flat = p.flat;
         a.tpg = p.tpg;
         a.gs_in = p.gs_in;
@@ -544,9 +549,7 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
             m.alpha = (T)p.alpha;
             return launch_cols_mid(m, dim3(p.grid), p.block, p.shmem, s);
         }
-        unsigned gx = p.grid;
-        if (ng > 1 && (int)p.grid < p.ntiles) gx = std::max(1u, (p.grid + (unsigned)ng - 1) / (unsigned)ng);
-        return launch_cols(a, dim3(gx, ng), p.block, p.shmem, s);
+        return launch_cols(a, dim3(ng > 1 ? cols_grid(p, ng) : p.grid, ng), p.block, p.shmem, s);
     }
     case P_POISSON:
         return launch_spectral<T>((const V*)src, (V*)dst, p.n0, p.n1, p.n2c, p.nz, p.op, (T)p.scale, (T)p.alpha,
@@ -1818,18 +1821,38 @@ static const void* plane_fn(int prec, const Pass& p)
     });
 }
 
-// Resident grid over p.ntiles, balanced as in strided_grid (a plane pass reads
-// a workgroup's next tile while its last one is transformed).  The kernels
-// take 65 to 128 registers, so sixteen wavefronts share a CU.
-static void resident_grid(const Plan& plan, Pass& p)
+// Workgroups of a plane or columns pass that share a CU: as many as the LDS
+// holds and the tiles fill.
+static int sharing(size_t lds, long long tiles, int cus)
 {
-    const size_t per_cu = std::max<size_t>(1, std::min(kLdsMax / p.shmem, (size_t)(1024 / p.block)));
-    const long long cap = (long long)plan.cus * (long long)per_cu;
-    p.grid = (unsigned)p.ntiles;
-    if (p.ntiles > cap) {
-        const long long rounds = (p.ntiles + cap - 1) / cap;
-        p.grid = (unsigned)((p.ntiles + rounds - 1) / rounds);
-    }
+    const long long fill = (tiles + cus - 1) / cus;
+    return (int)std::max<long long>(1, std::min<long long>(std::min<long long>((long long)(kLdsMax / lds), 8), fill));
+}
+
+// Workgroup and grid of a plane pass over ng transforms: sixteen wavefronts
+// (the kernels take 65 to 128 registers) divided among the workgroups that
+// share a CU, but no more than a tile can use; a resident grid, balanced as
+// in strided_grid (a workgroup's next tile is read while its last one is
+// transformed).  Twelve 48^3 transforms at once with nine wavefronts per
+// plane, so one plane per CU: 21 us, the two passes they replace 22 us.
+static void plane_launch(const Pass& p, int ng, unsigned* grid, unsigned* block)
+{
+    const int share = sharing(p.shmem, (long long)p.ntiles * ng, p.cus);
+    const int waves = std::max(1, std::min(16 / share, p.need_waves));
+    *block = (unsigned)(waves * 64);
+    const long long per_cu = std::max<long long>(1, std::min<long long>((long long)(kLdsMax / p.shmem), 16 / waves));
+    const long long cap = p.cus * per_cu, total = (long long)p.ntiles * ng;
+    const long long rounds = (total + cap - 1) / cap;
+    *grid = (unsigned)((total + rounds - 1) / rounds);
+}
+
+// Grid of a columns pass over ng transforms, likewise.
+static unsigned cols_grid(const Pass& p, int ng)
+{
+    const long long per_cu = std::max<long long>(1, std::min<long long>((long long)(kLdsMax / p.shmem), 1024 / p.block));
+    const long long cap = std::max<long long>(1, p.cus * per_cu / ng);
+    const long long rounds = (p.ntiles + cap - 1) / cap;
+    return (unsigned)((p.ntiles + rounds - 1) / rounds);
 }
 
 // A plane pass of `tiles` planes of A rows from the z-pass (whose variant and
@@ -1847,7 +1870,7 @@ static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool
     // 26.2, 200 planes 39.6 against 36.1, 1024 planes 169 against 115).  Smaller
     // planes pay at any count (2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64
     // 15.7 against 13.5).
-    if (!split && 2 * lds > kLdsMax && 4LL * tiles < 3LL * plan.cus) return MIFFT_OK;
+    if (!split && 2 * lds > kLdsMax && 4LL * tiles * plan.copies < 3LL * plan.cus) return MIFFT_OK;
     p.kind = z.kind == P_R2C ? P_PLANE_R2C : z.kind == P_C2R ? P_PLANE_C2R : P_PLANE;
     p.L = z.L;
     if (!plane_fn(plan.prec, p)) return MIFFT_OK;
@@ -1857,17 +1880,14 @@ static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool
     p.tag = 0;
     int rc = get_twiddles(plan, A, (void**)&p.twy);
     if (rc) return rc;
-    // 512 threads where two or more workgroups share a CU, but no more
-    // wavefronts than the rows, or eight elements per thread, need
+    // wavefronts that the rows, or four elements per thread, keep busy
     const int lpw = 64 / zline_threads(z.L, plan.prec == MIFFT_FP64);
-    const int want = (2 * lds <= kLdsMax && tiles >= 2 * plan.cus) ? 512 : 1024;
-    const int need = std::max((A + lpw - 1) / lpw, A * z.L / 256);
-    const int waves = std::max(1, std::min(want / 64, need));
-    p.lines_per_wg = waves * lpw;
-    p.block = (unsigned)(waves * 64);
+    p.need_waves = std::min(16, std::max((A + lpw - 1) / lpw, A * z.L / 256));
+    p.lines_per_wg = lpw;
     p.shmem = lds;
     p.ntiles = tiles;
-    resident_grid(plan, p);
+    p.cus = plan.cus;
+    plane_launch(p, 1, &p.grid, &p.block);
     *ok = true;
     return MIFFT_OK;
 }
@@ -1923,7 +1943,7 @@ struct Split {
 
 static size_t cols_lds(const Plan& plan, int B, int C)
 {
-    return ((size_t)plan.n0 * B * C + plan.n0) * plan.esz + 2 * (size_t)plan.n0;
+    return ((size_t)plan.n0 * cols_pitch(B, C, (int)plan.esz) + plan.n0) * plan.esz + 2 * (size_t)plan.n0;
 }
 
 // Threads of a columns tile: a multiple of its row B C, 512 where two share a
@@ -1932,7 +1952,7 @@ static int cols_threads(const Plan& plan, int B, int C, long long tiles)
 {
     const int P = B * C, slots = kColsHeld / (int)plan.esz / B; // rows of C per thread
     for (int want : {512, 1024}) {
-        if (want == 512 && (2 * cols_lds(plan, B, C) > kLdsMax || tiles <= plan.cus)) continue;
+        if (want == 512 && (2 * cols_lds(plan, B, C) > kLdsMax || tiles * plan.copies <= plan.cus)) continue;
         const int t = std::min(want, plan.n0 * P) / P * P;
         if (t > 0 && slots * (t / C) >= plan.n0) return t;
     }
@@ -1940,22 +1960,25 @@ static int cols_threads(const Plan& plan, int B, int C, long long tiles)
 }
 
 // The split with the least estimated time of its two passes, relative to
-// passes whose tiles share a CU (and overlap) and whose rows are whole
-// 128-byte lines; false where three passes are as good.  Measured (three
-// passes against two, us): all shared, 16 x 256 KiB rows: 128 x 256 x 256 FP32
-// 82 -> 61; the plane alone on its CU: 256^3 FP32 C2C 152 -> 115, R2C 95 -> 72;
-// both alone, 128-byte rows: 256^3 FP64 R2C 180 -> 137, C2R 152 -> 137; both
-// alone, 64-byte rows: 256^3 FP64 C2C 297 -> 330, 1024 x 64 x 512 FP32 323 -> 328;
-// 64-byte rows that straddle lines: 500 x 200 x 180 FP32 210 -> 225.  Spectral
-// solves (five passes against three; B, C): 256^3 FP32 157 us, 2,16 127, 4,8 137;
-// FP64 251, 4,4 210, 4,8 227; 128^3 FP64 61, 4,8 46, 2,8 50.
+// passes whose tiles share a CU (and overlap), whose rows are whole 128-byte
+// lines and whose x-axis takes the usual number of stages; none where three
+// passes are as good.  Measured (three passes against two, us): all shared,
+// 128 x 256 x 256 FP32 82 -> 58; the plane alone on its CU, 256^3 FP32 C2C
+// 154 -> 115, R2C 96 -> 71; both alone, 128-byte rows, 256^3 FP64 R2C 180 -> 137,
+// C2R 152 -> 139; both alone, 64-byte rows, 256^3 FP64 C2C 297 -> 330, 1024 x 64 x
+// 512 FP32 323 -> 328; 64-byte rows that straddle lines and a third stage along
+// x, 500 x 200 x 180 FP32 210 -> 225; one workgroup of more than half a CU's
+// wavefronts, 125^3 FP32 35 -> 38.  Spectral solves (five passes against three;
+// B, C): 256^3 FP32 157 us, 2,16 127, 4,8 137; FP64 251, 4,4 210, 4,8 227; 128^3
+// FP64 61, 4,8 46, 2,8 50.
 // `inner`: both of the second pass's sides are internal (rows padded to whole
 // lines, tiles of one group: the last one may be nearly empty).
 static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
 {
     int fb = 0, fc = 0; // MIFFT_SPLIT=B,C: that split where it fits (comparison, tests)
     if (const char* e = getenv("MIFFT_SPLIT")) sscanf(e, "%d,%d", &fb, &fc);
-    double best = fb ? 1e9 : inner ? 2.4 : 2.35;
+    double best = fb ? 1e9 : 2.4;
+    const double stages = plane_radices(plan.n0, plan.prec == MIFFT_FP64).n > (plan.prec == MIFFT_FP64 ? 3 : 2) ? 1.1 : 1.0;
     size_t best_cl = 0;
     bool found = false;
     for (int B : {2, 3, 4, 5, 6, 8}) {
@@ -1968,7 +1991,8 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
                 continue;
             double rows = row >= 128 ? 1.0 : inner ? 1.2 : (size_t)nc * plan.esz % 128 == 0 ? 1.1 : 1.25;
             if (inner) rows *= (double)((nc + C - 1) / C * C) / nc;
-            const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (2 * cl > kLdsMax ? 1.2 : 1.0) * rows;
+            const double wide = cols_threads(plan, B, C, 1 << 20) > 512 ? 0.05 : 0.0; // sixteen wavefronts fill a CU
+            const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (2 * cl > kLdsMax ? 1.2 : 1.0 + wide) * rows * stages;
             if (cost < best || (cost == best && cl > best_cl)) { // the larger tile: less set-up
                 best = cost;
                 best_cl = cl;
@@ -2004,7 +2028,7 @@ static int build_split(Plan& plan)
     // against 37.8.
     auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
     if (!W && !getenv("MIFFT_SPLIT") &&
-        (2 * cols_lds(plan, B, sp.C) > kLdsMax || (!real && pow2(n1) && pow2(plan.n2))))
+        (cols_threads(plan, B, sp.C, 1 << 20) > 512 || (!real && pow2(n1) && pow2(plan.n2))))
         return MIFFT_OK;
     const long long plane = (long long)n1 * nc;
     // 32-bit offsets inside a tile
@@ -2085,7 +2109,8 @@ static int build_split(Plan& plan)
         const size_t out_bytes = (size_t)n0 * plane * plan.esz;
         a.nt_out = c2r && out_bytes >= ((size_t)128 << 20);
         c.nt_out = out_bytes > ((size_t)256 << 20);
-        resident_grid(plan, c);
+        c.cus = plan.cus;
+        c.grid = cols_grid(c, 1);
         (dir ? plan.plane_inv : plan.plane_fwd) = c2r ? std::vector<Pass>{c, a} : std::vector<Pass>{a, c};
         if (plan.plane_oop) {
             a.dst = c.src = B_WS;
@@ -2152,7 +2177,8 @@ static int build_split_spectral(Plan& plan)
     c.ntiles = A * c.tpg;
     c.shmem = cols_lds(plan, B, sp.C);
     c.block = (unsigned)cols_threads(plan, B, sp.C, c.ntiles);
-    resident_grid(plan, c);
+    c.cus = plan.cus;
+    c.grid = cols_grid(c, 1);
     plan.plane_poisson = {a, c, b};
     plan.plane_mul = 1;
     plan.spec_bytes = (bytes + 255) / 256 * 256;

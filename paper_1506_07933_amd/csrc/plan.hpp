@@ -98,6 +98,7 @@ struct Pass {
     // split y-axis: plane tiles (x, b) of nb per x, rows b s_b apart; the
     // columns pass takes nb points of y1 and split_C columns of k2 per tile
     int nb = 1, split_C = 0, flat = 0;
+    int need_waves = 0, cus = 256; // plane passes: wavefronts a tile can use
     int split_tw = 0; // results take the factors w_n1^{y1 ka}
     long long is_b = 0, os_b = 0, ys_in = 0, ys_out = 0;
     const void* twn = nullptr; // length n1
@@ -154,6 +155,7 @@ public:
     int slab_p = 1;
     // arrays of rank > 3 (Algorithm 2): the extents, first (slowest) to last;
     // n0 n1 n2 then hold (product of the leading extents, second-to-last, last)
+    int copies = 1; // transforms of this shape that a batch launches together
     bool nd = false;
     std::vector<int> dims;
     Pass sz, sy, sy_pack, spk, sx, sxi, supk, syi, syi_unpack, szi;
@@ -256,6 +258,8 @@ int build_slab(Plan& plan, unsigned flags);
 int build_nd(Plan& plan, unsigned flags);
 // Fuse the z- and y-passes of a built plan's lists into plane passes (untuned plans).
 int build_planes(Plan& plan);
+// mifft_plan_create for a batch that launches `copies` such transforms together.
+int plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int prec, unsigned flags, int copies);
 
 const void* cols_kernel(bool fp64, bool mid = false);
 hipError_t launch_cols_mid(const MidArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);

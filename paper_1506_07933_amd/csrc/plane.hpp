@@ -54,7 +54,8 @@ struct ColPlan {
 template <typename T> struct PlaneArgs {
     const void* in;
     void* out;
-    GroupPtrs<T> grp;     // grouped launches, as in ContigArgs
+    GroupPtrs<T> grp;     // ng > 1 transforms of one shape: their tiles one after another
+    int ng;
     const cx<T>* twz;     // z-lines, length L
     const cx<T>* tw2;     // real: exp(-2 pi i k / n2)
     const cx<T>* twy;     // columns, length A
@@ -575,22 +576,26 @@ template <typename T, int L> struct ZRows {
 };
 
 // Forward planes: REAL: rows of 2L reals, C = L + 1 outputs; else C = L.
-template <typename T, int L, bool REAL>
-__device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>* __restrict__ ain,
-                                              cx<T>* __restrict__ aout)
+// src(m), dst(m): the buffers of transform m (0 unless several run at once).
+template <typename T, int L, bool REAL, typename Src, typename Dst>
+__device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, Src&& src, Dst&& dst)
 {
     using V = cx<T>;
     constexpr int C = REAL ? L + 1 : L, PITCH = plane_pitch(L, sizeof(T) == 8);
     extern __shared__ __align__(16) unsigned char smem_raw[];
     V* tile = reinterpret_cast<V*>(smem_raw);
     const int A = a.cp.A;
+    const int total = a.ntiles * a.ng;
     int x = blockIdx.x;
-    if (x >= a.ntiles) return; // uniform
+    if (x >= total) return; // uniform
     const ZRows<T, L> zr;
     ZForward<T, L> c;
     c.t = zr.t;
     c.sgn = REAL ? T(1) : a.sgn;
-    auto in_of = [&](int t) { return ain + (long long)(t / a.nb) * a.is_x + (long long)(t % a.nb) * a.is_b; };
+    auto in_of = [&](int i) {
+        const int m = REAL || a.ng == 1 ? 0 : i / a.ntiles, t = i - m * a.ntiles;
+        return src(m) + (long long)(t / a.nb) * a.is_x + (long long)(t % a.nb) * a.is_b;
+    };
     const V* in = in_of(x);
     if (zr.first < A) c.load(in + (long long)zr.row(zr.first, A) * a.is_r);
     ColCtx<T> cc;
@@ -605,13 +610,14 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
     __syncthreads();
     for (;;) {
         const int xn = x + (int)gridDim.x;
-        const V* next_in = xn < a.ntiles ? in_of(xn) : in;
-        cc.b = x % a.nb;
+        const V* next_in = xn < total ? in_of(xn) : in;
+        const int m = REAL || a.ng == 1 ? 0 : x / a.ntiles, t = x - m * a.ntiles;
+        cc.b = t % a.nb;
         if (cc.b > 0)
             for (int i = threadIdx.x; i < A; i += blockDim.x) twb[i] = a.twn[cc.b * i];
         for (int r0 = zr.first; r0 < A; r0 += zr.step) {
             const bool last = r0 + zr.step >= A;
-            c.has_next = !last || xn < a.ntiles;
+            c.has_next = !last || xn < total;
             c.nin = (last ? next_in : in) + (long long)zr.row(last ? zr.first : r0 + zr.step, A) * a.is_r;
             c.row = tile + zr.row(r0, A) * PITCH;
             // as in k_strided: no address of this is kept across the loops
@@ -634,13 +640,13 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
             }
         }
         __syncthreads();
-        cc.out = aout + (long long)(x / a.nb) * a.os_x + (long long)cc.b * a.os_b;
+        cc.out = dst(m) + (long long)(t / a.nb) * a.os_x + (long long)cc.b * a.os_b;
         for (int i = 0; i + 1 < a.cp.n; ++i) {
             col_dispatch<T, C, PITCH, COL_LDS>(cc, a.cp.s[i], A);
             __syncthreads();
         }
         col_dispatch<T, C, PITCH, COL_STORE>(cc, a.cp.s[a.cp.n - 1], A);
-        if (xn >= a.ntiles) break;
+        if (xn >= total) break;
         __syncthreads(); // the next tile's rows overwrite this one's
         x = xn;
         in = next_in;
@@ -650,19 +656,19 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, const cx<T>
 template <typename T, int L>
 __global__ __launch_bounds__(1024) void k_plane(PlaneArgs<T> a)
 {
-    const cx<T>* ain = reinterpret_cast<const cx<T>*>(a.in);
-    cx<T>* aout = reinterpret_cast<cx<T>*>(a.out);
-    if (gridDim.y > 1) {
-        ain = a.grp.in[blockIdx.y];
-        aout = a.grp.out[blockIdx.y];
-    }
-    plane_forward<T, L, false>(a, ain, aout);
+    // (indexing the argument itself in plane_forward would copy it to scratch memory)
+    const auto* args = (const __attribute__((address_space(4))) PlaneArgs<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+    plane_forward<T, L, false>(
+        a, [&](int m) { return a.ng == 1 ? reinterpret_cast<const cx<T>*>(a.in) : args->grp.in[m]; },
+        [&](int m) { return a.ng == 1 ? reinterpret_cast<cx<T>*>(a.out) : args->grp.out[m]; });
 }
 
 template <typename T, int L>
 __global__ __launch_bounds__(1024) void k_plane_r2c(PlaneArgs<T> a)
 {
-    plane_forward<T, L, true>(a, reinterpret_cast<const cx<T>*>(a.in), reinterpret_cast<cx<T>*>(a.out));
+    plane_forward<T, L, true>(
+        a, [&](int) { return reinterpret_cast<const cx<T>*>(a.in); },
+        [&](int) { return reinterpret_cast<cx<T>*>(a.out); });
 }
 
 template <typename T, int L>
