@@ -34,6 +34,7 @@ struct mifft_batch_s {
     int count = 0, prec = MIFFT_FP32;
     bool kernels = false; // per-pass kernel launches instead of the persistent kernel
     bool grouped = false; // kernels: each pass of all transforms of one shape as one launch
+    bool planes = false;  // persistent: plane items where planes fit LDS (untuned batches)
     std::vector<int> dims;
     // persistent path
     std::vector<mifft::BatchPass> passes;
@@ -79,6 +80,8 @@ static const int kMenu[] = {
 #undef MIFFT_BATCH_LEN
 };
 static const int kMenuN = (int)(sizeof(kMenu) / sizeof(kMenu[0]));
+
+static const size_t kBatchPlaneLds = 160 * 1024 - 256; // (the kernel's own bookkeeping takes the rest)
 
 static int menu_code(int L)
 {
@@ -129,13 +132,58 @@ static int build_queue(mifft_batch_s* b)
     std::vector<BatchPass>& P = b->passes;
     std::vector<int> last(count, -1); // index of each transform's latest pass
     size_t max_lds = 0; // dynamic LDS elements of the largest pass
-    // data per queue item (MIFFT_BATCH_ITEM_KIB overrides the 128 KiB default;
-    // untuned 64-transform batch: 64 KiB 1.09 ms, 128 KiB 1.04, 256 KiB 1.03)
+    // data per queue item (MIFFT_BATCH_ITEM_KIB overrides the default: 128 KiB --
+    // untuned 64-transform batch: 64 KiB 1.09 ms, 128 KiB 1.04, 256 KiB 1.03 -- or,
+    // with plane items, 256 KiB: 128 KiB 0.83 ms, 256 KiB 0.75, 512 KiB 0.70, but 8
+    // transforms 139, 134 and 168 us)
     size_t default_item = 128 * 1024;
+    bool item_set = false;
     if (const char* e = getenv("MIFFT_BATCH_ITEM_KIB")) {
         const long v = atol(e);
-        if (v > 0 && v <= 64 * 1024) default_item = (size_t)v * 1024;
+        if (v > 0 && v <= 64 * 1024) {
+            default_item = (size_t)v * 1024;
+            item_set = true;
+        }
     }
+    // Transforms with plane items.  A plane of more than half of LDS leaves one
+    // workgroup per CU, for every item of the batch: only where such
+    // transforms are most of it.
+    std::vector<size_t> plane_lds(count, 0); // LDS of a plane item, 0: z- and y-items
+    if (b->planes) {
+        double all = 0, large = 0;
+        for (int t = 0; t < count; ++t) {
+            const int n1 = dims[3 * t + 1], n2 = dims[3 * t + 2];
+            const double data = (double)dims[3 * t] * n1 * n2;
+            all += data;
+            if (n1 < 2 || n2 < 2) continue;
+            const size_t lds = ((size_t)n1 * plane_pitch(n2, prec == MIFFT_FP64) + n2 + 2 * (size_t)n1) * esz;
+            if (lds > kBatchPlaneLds) continue;
+            plane_lds[t] = lds;
+            if (lds > kBatchPlaneLds / 2) large += data;
+        }
+        if (large < 0.5 * all)
+            for (size_t& v : plane_lds)
+                if (v > kBatchPlaneLds / 2) v = 0;
+    }
+    size_t max_plane = 0;
+    if (!item_set && std::any_of(plane_lds.begin(), plane_lds.end(), [](size_t v) { return v > 0; }))
+        default_item = 256 * 1024;
+    auto twiddles = [&](int L, void** out) -> int {
+        auto it = b->tw.find(L);
+        if (it == b->tw.end()) {
+            void* w = nullptr;
+            if (hipMalloc(&w, (size_t)L * esz) != hipSuccess) return set_error(MIFFT_ERR_NOMEM, "twiddles");
+            hipError_t e = prec == MIFFT_FP64 ? launch_twiddles<double>((cx<double>*)w, L, nullptr)
+                                              : launch_twiddles<float>((cx<float>*)w, L, nullptr);
+            if (e != hipSuccess) {
+                hipFree(w);
+                return set_error(MIFFT_ERR_DEVICE, "twiddle kernel: %s", hipGetErrorString(e));
+            }
+            it = b->tw.emplace(L, w).first;
+        }
+        *out = it->second;
+        return MIFFT_OK;
+    };
     for (int stage = 0; stage < 3; ++stage) {
         // Within a stage the passes are ordered by line length, so that the
         // workgroups running at any moment mostly execute the same
@@ -148,6 +196,31 @@ static int build_queue(mifft_batch_s* b)
             const int n0 = dims[3 * t], n1 = dims[3 * t + 1], n2 = dims[3 * t + 2];
             const int L = stage == 0 ? n2 : (stage == 1 ? n1 : n0);
             if (L == 1) continue;
+            if (plane_lds[t] && stage == 1) continue;
+            if (plane_lds[t] && stage == 0) {
+                BatchPass p{};
+                p.kind = 2;
+                p.code = menu_code(n2);
+                p.L = n2;
+                p.tpl = zline_threads(n2, prec == MIFFT_FP64);
+                p.xform = t;
+                p.from_in = 1;
+                p.units = p.subtiles = n0;
+                p.per_wave = 1;
+                p.sub_per_item = (int)std::max<size_t>(1, default_item / ((size_t)n1 * n2 * esz));
+                p.nitems = (n0 + p.sub_per_item - 1) / p.sub_per_item;
+                p.stage = 0;
+                p.dep = -1;
+                p.done = (int)P.size();
+                if (!make_col_plan(prec, n1, &p.cp)) return set_error(MIFFT_ERR_INVALID, "internal: no column plan");
+                int rc;
+                if ((rc = twiddles(n2, const_cast<void**>(&p.tw))) || (rc = twiddles(n1, const_cast<void**>(&p.twy))))
+                    return rc;
+                last[t] = (int)P.size();
+                P.push_back(p);
+                max_plane = std::max(max_plane, plane_lds[t]);
+                continue;
+            }
             int var = 0;
             size_t item_bytes = default_item;
             auto ch = b->choice.find({stage, L});
@@ -195,19 +268,7 @@ static int build_queue(mifft_batch_s* b)
             p.dep_target = last[t] >= 0 ? P[last[t]].nitems : 0;
             p.dep_stage = last[t] >= 0 ? P[last[t]].stage : 0;
             p.done = (int)P.size();
-            auto it = b->tw.find(L);
-            if (it == b->tw.end()) {
-                void* w = nullptr;
-                if (hipMalloc(&w, (size_t)L * esz) != hipSuccess) return set_error(MIFFT_ERR_NOMEM, "twiddles");
-                hipError_t e = prec == MIFFT_FP64 ? launch_twiddles<double>((cx<double>*)w, L, nullptr)
-                                                  : launch_twiddles<float>((cx<float>*)w, L, nullptr);
-                if (e != hipSuccess) {
-                    hipFree(w);
-                    return set_error(MIFFT_ERR_DEVICE, "twiddle kernel: %s", hipGetErrorString(e));
-                }
-                it = b->tw.emplace(L, w).first;
-            }
-            p.tw = it->second;
+            if (const int rc = twiddles(L, const_cast<void**>(&p.tw))) return rc;
             last[t] = (int)P.size();
             P.push_back(p);
             max_lds = std::max(max_lds, (size_t)batch_lds_elems(L, p.tpl, prec == MIFFT_FP32));
@@ -221,7 +282,7 @@ static int build_queue(mifft_batch_s* b)
     }
     b->total_items = start;
     b->ncounters = (int)P.size() + 2 + kBatchStages;
-    b->lds = max_lds * esz;
+    b->lds = std::max(max_lds * esz, max_plane);
     if (b->lds > 160 * 1024)
         return set_error(MIFFT_ERR_UNSUPPORTED, "the chosen code paths need %zu bytes of LDS per workgroup", b->lds);
     std::vector<int> item_pass((size_t)b->total_items);
@@ -433,6 +494,9 @@ int batch_create(mifft_batch* out, int count, const int* dims, int kind, int pre
             const int v = atoi(e);
             if (v > 0) b->publish_every = v;
         }
+        // a tuned batch runs the items that the tuner times; MIFFT_PLANES=0 keeps them too
+        const char* pe = getenv("MIFFT_PLANES");
+        b->planes = !(flags & MIFFT_TUNE) && !(pe && atoi(pe) == 0);
         int rc = (flags & MIFFT_TUNE) ? tune_batch(b) : build_queue(b);
         if (rc) {
             delete b;

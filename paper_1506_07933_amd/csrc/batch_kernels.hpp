@@ -27,6 +27,10 @@
 // leaves, publishing then.  Every wait is bounded as well: a wait that
 // exceeds its bound raises an abort flag that makes every workgroup leave.
 //
+// A transform whose planes fit LDS has plane items instead of z- and y-items
+// (stage 0): the workgroup transforms whole planes along z and y between one
+// read and one write (plane.hpp), and the x-pass waits for them.
+//
 // Inside a z-item each wavefront transforms its own contiguous lines,
 // synchronising only within the wavefront.  A y- or x-item is a run of
 // column tiles that the whole workgroup transforms one after another: a
@@ -40,7 +44,7 @@
 
 #include <stddef.h>
 
-#include "kernels.hpp"
+#include "plane.hpp"
 
 namespace mifft {
 
@@ -100,7 +104,7 @@ __host__ __device__ constexpr bool batch_var_distinct(int L, int v)
 }
 
 struct BatchPass {
-    int kind;     // 0: contiguous z-lines, 1: strided columns
+    int kind;     // 0: contiguous z-lines, 1: strided columns, 2: planes of cp.A rows of L
     int code;     // kBatchVariants x menu index of the line length + variant
     int L;
     int tpl;      // threads per line
@@ -121,6 +125,8 @@ struct BatchPass {
     int dep_stage;       // stage of that pass
     int done;            // completion counter of this pass
     const void* tw;      // twiddles of length L
+    const void* twy;     // kind 2: of length cp.A
+    ColPlan cp;
 };
 
 template <typename T> struct BatchArgs {
@@ -469,6 +475,98 @@ __device__ __forceinline__ void batch_dispatch(int code, const BatchPass* p, con
     }
 }
 
+// Planes first .. last - 1 of a transform (the whole workgroup, forward).
+template <typename T, int L>
+__device__ __noinline__ void batch_plane(const BatchPass* pp, const cx<T>* src, cx<T>* dst, int first, int last,
+                                         MIFFT_LDS typename vec2_of<T>::type* lds)
+{
+    using V = cx<T>;
+    constexpr int PITCH = plane_pitch(L, sizeof(T) == 8);
+    const MIFFT_CONST BatchPass* p = (const MIFFT_CONST BatchPass*)pp;
+    const int A = __builtin_amdgcn_readfirstlane(p->cp.A), n = __builtin_amdgcn_readfirstlane(p->cp.n);
+    // (address spaces the compiler sees through: LDS and global accesses, not flat ones)
+    V* tile = (V*)lds;
+    const V* in = (const V*)(const MIFFT_GLOBAL V*)src;
+    V* out = (V*)(MIFFT_GLOBAL V*)dst;
+    const V* twz = (const V*)(const MIFFT_GLOBAL V*)p->tw;
+    const V* twy = (const V*)(const MIFFT_GLOBAL V*)p->twy;
+    const ZRows<T, L> zr(kBatchWaves);
+    ZForward<T, L> c;
+    c.t = zr.t;
+    c.sgn = T(1);
+    const long long plane = (long long)A * L;
+    if (zr.first < A) c.load(in + first * plane + (long long)zr.row(zr.first, A) * L);
+    V* tw = tile + A * PITCH;
+    V* ty = tw + L;
+    unsigned short* rev = (unsigned short*)(ty + A);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < L; i += kBatchBlock) tw[i] = twz[i];
+    for (int i = tid; i < A; i += kBatchBlock) {
+        ty[i] = twy[i];
+        int q = i, k = 0, mul = 1; // digit_reverse
+        for (int s = 0; s < n; ++s) {
+            const int qs = p->cp.s[s].q;
+            const int d = qs > 1 ? (int)__umulhi((uint32_t)q, p->cp.s[s].mq) : q;
+            q -= d * qs;
+            k += d * mul;
+            mul *= p->cp.s[s].R;
+        }
+        rev[i] = (unsigned short)k;
+    }
+    c.twd = tw;
+    ColCtx<T> cc;
+    cc.tile = tile;
+    cc.tw = ty;
+    cc.rev = rev;
+    cc.in = nullptr;
+    cc.rs = L;
+    cc.sgn = T(1);
+    cc.nt = false;
+    cc.twb = nullptr;
+    cc.b = 0;
+    cc.threads = kBatchBlock;
+    __syncthreads();
+    for (int x = first; x < last; ++x) {
+        for (int r0 = zr.first; r0 < A; r0 += zr.step) {
+            const bool end = r0 + zr.step >= A;
+            c.has_next = !end || x + 1 < last;
+            c.nin = in + (end ? x + 1 : x) * plane + (long long)zr.row(end ? zr.first : r0 + zr.step, A) * L;
+            c.row = tile + zr.row(r0, A) * PITCH;
+            asm volatile("" : "+v"(c.t));
+            ZStage<T, L, 0, 1, decltype(c)>::run(c);
+        }
+        __syncthreads();
+        cc.out = out + x * plane;
+        for (int s = 0; s < n; ++s) {
+            ColStage cs;
+            cs.R = p->cp.s[s].R;
+            cs.q = p->cp.s[s].q;
+            cs.tws = p->cp.s[s].tws;
+            cs.mq = p->cp.s[s].mq;
+            if (s + 1 < n)
+                col_dispatch<T, L, PITCH, COL_LDS>(cc, cs, A);
+            else
+                col_dispatch<T, L, PITCH, COL_STORE>(cc, cs, A);
+            __syncthreads(); // (after the last stage: before the next plane's rows)
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void batch_plane_dispatch(int menu, const BatchPass* p, const cx<T>* src, cx<T>* dst,
+                                                     int first, int last, MIFFT_LDS typename vec2_of<T>::type* lds)
+{
+    switch (menu) {
+#define MIFFT_BATCH_CASE(I, LEN)                                 \
+    case I: batch_plane<T, LEN>(p, src, dst, first, last, lds); \
+        break;
+        MIFFT_BATCH_MENU(MIFFT_BATCH_CASE)
+#undef MIFFT_BATCH_CASE
+    default:
+        break;
+    }
+}
+
 // Take the next queue item (or the end of the queue once the abort flag is up).
 __device__ __forceinline__ int batch_dequeue(int* head, int* abort_flag, int total)
 {
@@ -618,8 +716,12 @@ template <typename T> __global__ __launch_bounds__(kBatchBlock) __attribute__((a
         V* dst = outs[xform];
         const int first = (item - item_start) * spi;
         const int last = first + spi < subtiles ? first + spi : subtiles;
-        batch_dispatch<T>(code, pp, src, dst, first, last, wave, lane,
-                          (MIFFT_LDS typename vec2_of<T>::type*)(size_t)lds_base);
+        if (__builtin_amdgcn_readfirstlane(pp->kind) == 2)
+            batch_plane_dispatch<T>(code, pp, src, dst, first, last,
+                                    (MIFFT_LDS typename vec2_of<T>::type*)(size_t)lds_base);
+        else
+            batch_dispatch<T>(code, pp, src, dst, first, last, wave, lane,
+                              (MIFFT_LDS typename vec2_of<T>::type*)(size_t)lds_base);
         // 4. thread 0: note the completion, prepare the next item
         __syncthreads();
         if (tid == 0) {

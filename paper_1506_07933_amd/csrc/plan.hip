@@ -1784,14 +1784,10 @@ int build_nd(Plan& plan, unsigned /*flags*/)
 // ---------------------------------------------------------- plane passes
 
 // The in-place column transform of A rows.
-static const ColPlan* col_plan(Plan& plan, int A)
+bool make_col_plan(int prec, int A, ColPlan* cp)
 {
-    for (const ColPlan& c : plan.col_plans)
-        if (c.A == A) return &c;
-    const PlaneRadices f = plane_radices(A, plan.prec == MIFFT_FP64);
-    if (f.n == 0) return nullptr;
-    plan.col_plans.push_back(ColPlan{});
-    ColPlan* cp = &plan.col_plans.back();
+    const PlaneRadices f = plane_radices(A, prec == MIFFT_FP64);
+    if (f.n == 0) return false;
     cp->A = A;
     cp->n = f.n;
     int q = A;
@@ -1803,7 +1799,17 @@ static const ColPlan* col_plan(Plan& plan, int A)
         s.q = q;
         s.mq = q > 1 ? (uint32_t)(((1ull << 32) + q - 1) / q) : 0;
     }
-    return cp;
+    return true;
+}
+
+static const ColPlan* col_plan(Plan& plan, int A)
+{
+    for (const ColPlan& c : plan.col_plans)
+        if (c.A == A) return &c;
+    ColPlan cp{};
+    if (!make_col_plan(plan.prec, A, &cp)) return nullptr;
+    plan.col_plans.push_back(cp);
+    return &plan.col_plans.back();
 }
 
 static size_t plane_lds(const Plan& plan, int A, int L)

@@ -270,6 +270,7 @@ template <typename T> struct ColCtx {
     bool nt;
     const V* twb;                // COL_STORE: row k times twb[k] (b > 0), in LDS
     int b;
+    int threads;                 // of the workgroup
 };
 
 // C columns of rows of PITCH elements.  Global offsets within a tile fit 32
@@ -291,7 +292,7 @@ __device__ __forceinline__ void col_stage(const ColCtx<T>& x, const ColStage& s,
     const int total = nb * C;
     int u = threadIdx.x;
     asm volatile("" : "+v"(u)); // as in k_strided: nothing of this is kept across the tile loop
-    for (; u < total; u += blockDim.x) {
+    for (; u < total; u += x.threads) {
         const int b = u / C, c = u - b * C;
         int g = b;
         if (q > 1) g = (int)__umulhi((uint32_t)b, s.mq);
@@ -562,14 +563,14 @@ constexpr int plane_pitch(int L, bool fp64) { return L + (L >> line_shift(L, fp6
 template <typename T, int L> struct ZRows {
     using Z = ZShape<T, L>;
     int sub, t, first, step;
-    __device__ __forceinline__ ZRows()
+    __device__ __forceinline__ ZRows(int waves)
     {
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
         sub = lane / Z::TPL;
         t = lane - sub * Z::TPL;
         if (sub >= Z::LPW) sub = 0;
         first = w * Z::LPW;
-        step = ((int)blockDim.x >> 6) * Z::LPW;
+        step = waves * Z::LPW;
     }
     // row of this thread in the round that starts at r0
     __device__ __forceinline__ int row(int r0, int A) const { return r0 + sub < A ? r0 + sub : A - 1; }
@@ -588,7 +589,7 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, Src&& src, 
     const int total = a.ntiles * a.ng;
     int x = blockIdx.x;
     if (x >= total) return; // uniform
-    const ZRows<T, L> zr;
+    const ZRows<T, L> zr((int)blockDim.x >> 6);
     ZForward<T, L> c;
     c.t = zr.t;
     c.sgn = REAL ? T(1) : a.sgn;
@@ -606,6 +607,7 @@ __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, Src&& src, 
     cc.sgn = REAL ? T(1) : a.sgn;
     cc.nt = a.nt_out != 0;
     cc.in = nullptr;
+    cc.threads = blockDim.x;
     plane_tables<T>(a, L, tile + A * PITCH, cc, c.twd);
     __syncthreads();
     for (;;) {
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(1024) void k_plane_c2r(PlaneArgs<T> a)
     const int A = a.cp.A;
     const V* ain = reinterpret_cast<const V*>(a.in);
     V* aout = reinterpret_cast<V*>(a.out);
-    const ZRows<T, L> zr;
+    const ZRows<T, L> zr((int)blockDim.x >> 6);
     ZInverseReal<T, L> c;
     c.tw2 = a.tw2;
     c.nt = a.nt_out != 0;
@@ -693,6 +695,7 @@ __global__ __launch_bounds__(1024) void k_plane_c2r(PlaneArgs<T> a)
     cc.nt = false;
     cc.out = nullptr;
     cc.twb = nullptr;
+    cc.threads = blockDim.x;
     cc.b = 0;
     plane_tables<T>(a, L, tile + A * PITCH, cc, c.twd);
     __syncthreads();

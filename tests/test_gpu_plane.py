@@ -188,3 +188,29 @@ def test_split_spectral_operators(monkeypatch, split, shape, prec):
     assert rel_l2(d.cpu().numpy(), oracle.divergence(*[u.astype(np.float64) for u in v])) <= TOL[prec]
     np.testing.assert_array_equal(fd.cpu().numpy(), f)
     p.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_persistent_plane_items(prec):
+    """Plane items of the one-launch batch beside z- and y-items: the smallest
+    planes, lines that leave lanes idle, one plane per item and several, planes
+    too large for LDS; in place gives the same bits."""
+    from paper_1506_07933_amd import BatchPlan
+    shapes = [(3, 2, 2), (1, 128, 64), (40, 4, 3), (2, 125, 100), (9, 16, 256), (5, 250, 8), (2, 256, 256), (32, 45, 27)]
+    cd = np.complex64 if prec == "fp32" else np.complex128
+    data = [synth.uniform_complex(s, cd, seed=i) for i, s in enumerate(shapes)]
+    xs = [torch.from_numpy(d).cuda() for d in data]
+    outs = [torch.empty_like(x) for x in xs]
+    b = BatchPlan(shapes, prec)
+    print(b.describe().splitlines()[0], flush=True)
+    b.forward(xs, outs)
+    torch.cuda.synchronize()
+    assert not b.aborted()
+    for s, d, o in zip(shapes, data, outs):
+        assert rel_l2(o.cpu().numpy(), oracle.fft3d_c2c(d.astype(np.complex128), -1)) <= TOL[prec], s
+    b.forward(xs, xs)
+    torch.cuda.synchronize()
+    assert not b.aborted()
+    for x, o in zip(xs, outs):
+        assert torch.equal(x, o)
+    b.close()
