@@ -331,7 +331,8 @@ int mifft_spectral_divergence(mifft_plan plan, const void* vx, const void* vy, c
  * mifft_batch_create -- plan `count` (1 .. 128) independent 3-D C2C transforms
  * of uneven sizes (dims holds n0, n1, n2 per transform) that run as ONE
  * launch of a persistent kernel: workgroups pull (transform, pass, tile)
- * work items from a device queue in dependency order (all z-passes, then all
+ * work items from a device queue in dependency order (all z-passes -- of
+ * transforms whose planes fit LDS, z- and y-axis together --, then all other
  * y-passes, then all x-passes; a pass waits on a completion counter of the
  * previous pass of its transform).  Every axis length must be 2 .. 256 with
  * prime factors 2, 3, 5, unless MIFFT_BATCH_KERNELS asks for the per-pass
