@@ -156,7 +156,7 @@ static int build_queue(mifft_batch_s* b)
             const double data = (double)dims[3 * t] * n1 * n2;
             all += data;
             if (n1 < 2 || n2 < 2) continue;
-            const size_t lds = ((size_t)n1 * plane_pitch(n2, prec == MIFFT_FP64) + n2 + 2 * (size_t)n1) * esz;
+            const size_t lds = ((size_t)n1 * plane_pitch(n2, radices_of(n2, prec)) + n2 + 2 * (size_t)n1) * esz;
             if (lds > kBatchPlaneLds) continue;
             plane_lds[t] = lds;
             if (lds > kBatchPlaneLds / 2) large += data;
@@ -202,7 +202,7 @@ static int build_queue(mifft_batch_s* b)
                 p.kind = 2;
                 p.code = menu_code(n2);
                 p.L = n2;
-                p.tpl = zline_threads(n2, prec == MIFFT_FP64);
+                p.tpl = zline_threads(n2, radices_of(n2, prec));
                 p.xform = t;
                 p.from_in = 1;
                 p.units = p.subtiles = n0;

@@ -481,7 +481,7 @@ __device__ __noinline__ void batch_plane(const BatchPass* pp, const cx<T>* src, 
                                          MIFFT_LDS typename vec2_of<T>::type* lds)
 {
     using V = cx<T>;
-    constexpr int PITCH = plane_pitch(L, sizeof(T) == 8);
+    constexpr int PITCH = plane_pitch(L, ZShape<T, L>::f);
     const MIFFT_CONST BatchPass* p = (const MIFFT_CONST BatchPass*)pp;
     const int A = __builtin_amdgcn_readfirstlane(p->cp.A), n = __builtin_amdgcn_readfirstlane(p->cp.n);
     // (address spaces the compiler sees through: LDS and global accesses, not flat ones)

@@ -1783,10 +1783,21 @@ int build_nd(Plan& plan, unsigned /*flags*/)
 
 // ---------------------------------------------------------- plane passes
 
+// plane_radices(L), searched once per length and precision.
+PlaneRadices radices_of(int L, int prec)
+{
+    static std::mutex mu;
+    static PlaneRadices found[2][MIFFT_MAX_AXIS + 1]; // n = 0: not yet
+    PlaneRadices& f = found[prec == MIFFT_FP64][L];
+    std::lock_guard<std::mutex> g(mu);
+    if (f.n == 0) f = plane_radices(L, prec == MIFFT_FP64);
+    return f;
+}
+
 // The in-place column transform of A rows.
 bool make_col_plan(int prec, int A, ColPlan* cp)
 {
-    const PlaneRadices f = plane_radices(A, prec == MIFFT_FP64);
+    const PlaneRadices f = radices_of(A, prec);
     if (f.n == 0) return false;
     cp->A = A;
     cp->n = f.n;
@@ -1814,7 +1825,7 @@ static const ColPlan* col_plan(Plan& plan, int A)
 
 static size_t plane_lds(const Plan& plan, int A, int L)
 {
-    return ((size_t)A * plane_pitch(L, plan.prec == MIFFT_FP64) + L + 2 * (size_t)A + (A + 3) / 4) * plan.esz; // tile, tables (plane.hpp)
+    return ((size_t)A * plane_pitch(L, radices_of(L, plan.prec)) + L + 2 * (size_t)A + (A + 3) / 4) * plan.esz; // tile, tables (plane.hpp)
 }
 
 static const void* plane_fn(int prec, const Pass& p)
@@ -1887,7 +1898,7 @@ static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool
     int rc = get_twiddles(plan, A, (void**)&p.twy);
     if (rc) return rc;
     // wavefronts that the rows, or four elements per thread, keep busy
-    const int lpw = 64 / zline_threads(z.L, plan.prec == MIFFT_FP64);
+    const int lpw = 64 / zline_threads(z.L, radices_of(z.L, plan.prec));
     p.need_waves = std::min(16, std::max((A + lpw - 1) / lpw, A * z.L / 256));
     p.lines_per_wg = lpw;
     p.shmem = lds;
@@ -1984,7 +1995,7 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
     int fb = 0, fc = 0; // MIFFT_SPLIT=B,C: that split where it fits (comparison, tests)
     if (const char* e = getenv("MIFFT_SPLIT")) sscanf(e, "%d,%d", &fb, &fc);
     double best = fb ? 1e9 : 2.4;
-    const double stages = plane_radices(plan.n0, plan.prec == MIFFT_FP64).n > (plan.prec == MIFFT_FP64 ? 3 : 2) ? 1.1 : 1.0;
+    const double stages = radices_of(plan.n0, plan.prec).n > (plan.prec == MIFFT_FP64 ? 3 : 2) ? 1.1 : 1.0;
     size_t best_cl = 0;
     bool found = false;
     for (int B : {2, 3, 4, 5, 6, 8}) {

@@ -261,6 +261,7 @@ int build_planes(Plan& plan);
 // mifft_plan_create for a batch that launches `copies` such transforms together.
 int plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int prec, unsigned flags, int copies);
 
+PlaneRadices radices_of(int L, int prec);
 bool make_col_plan(int prec, int A, ColPlan* cp);
 const void* cols_kernel(bool fp64, bool mid = false);
 hipError_t launch_cols_mid(const MidArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);

@@ -233,9 +233,9 @@ constexpr PlaneRadices plane_radices(int L, bool fp64)
 
 // Threads per z-line: one first-stage butterfly each, or as many as keep the
 // line within a wavefront.
-constexpr int zline_threads(int L, bool fp64)
+constexpr int zline_threads(int L, const PlaneRadices& f)
 {
-    const int nbf = L / plane_radices(L, fp64).r[0];
+    const int nbf = L / f.r[0];
     const int per = (nbf + 63) / 64;
     return (nbf + per - 1) / per;
 }
@@ -244,13 +244,13 @@ constexpr int zline_threads(int L, bool fp64)
 // exchange (two stages): every 16, which still spreads the first stage's
 // writes, R apart, over the banks; more: every 8 (the second exchange's runs
 // of 8: 1024 x 64 x 512 with 512 = 8 8 8 took 307 us, 344 with one every 16).
-constexpr int line_shift(int L, bool fp64) { return plane_radices(L, fp64).n <= 2 ? 4 : 3; }
+constexpr int line_shift(const PlaneRadices& f) { return f.n <= 2 ? 4 : 3; }
 
 template <typename T, int L> struct ZShape {
     static constexpr PlaneRadices f = plane_radices(L, sizeof(T) == 8);
-    static constexpr int TPL = zline_threads(L, sizeof(T) == 8);
+    static constexpr int TPL = zline_threads(L, f);
     static constexpr int LPW = 64 / TPL; // lines per wavefront
-    static constexpr int SH = line_shift(L, sizeof(T) == 8);
+    static constexpr int SH = line_shift(f);
     static constexpr int R0 = f.r[0];
     static constexpr int SLOTS = ((L / R0 + TPL - 1) / TPL) * R0;
 };
@@ -555,7 +555,7 @@ __device__ __forceinline__ void plane_tables(const PlaneArgs<T>& a, int L, cx<T>
 }
 
 // Row pitch of the tile: a line's padded places, or its L + 1 outputs.
-constexpr int plane_pitch(int L, bool fp64) { return L + (L >> line_shift(L, fp64)) + 1; }
+constexpr int plane_pitch(int L, const PlaneRadices& f) { return L + (L >> line_shift(f)) + 1; }
 
 // Rows of a wavefront: LPW lines at a time; lanes past the last line repeat
 // the first line's threads (same values to the same places), and so do rows
@@ -582,7 +582,7 @@ template <typename T, int L, bool REAL, typename Src, typename Dst>
 __device__ __forceinline__ void plane_forward(const PlaneArgs<T>& a, Src&& src, Dst&& dst)
 {
     using V = cx<T>;
-    constexpr int C = REAL ? L + 1 : L, PITCH = plane_pitch(L, sizeof(T) == 8);
+    constexpr int C = REAL ? L + 1 : L, PITCH = plane_pitch(L, ZShape<T, L>::f);
     extern __shared__ __align__(16) unsigned char smem_raw[];
     V* tile = reinterpret_cast<V*>(smem_raw);
     const int A = a.cp.A;
@@ -677,7 +677,7 @@ template <typename T, int L>
 __global__ __launch_bounds__(1024) void k_plane_c2r(PlaneArgs<T> a)
 {
     using V = cx<T>;
-    constexpr int C = L + 1, PITCH = plane_pitch(L, sizeof(T) == 8);
+    constexpr int C = L + 1, PITCH = plane_pitch(L, ZShape<T, L>::f);
     extern __shared__ __align__(16) unsigned char smem_raw[];
     V* tile = reinterpret_cast<V*>(smem_raw);
     const int A = a.cp.A;
