@@ -478,8 +478,9 @@ int batch_create(mifft_batch* out, int count, const int* dims, int kind, int pre
             std::vector<int> key(dims + 3 * t, dims + 3 * t + 3);
             if (b->plans.count(key)) continue;
             mifft_plan p = nullptr;
-            int copies = 0;
+            int copies = 0; // launched together: only a grouped batch does that
             for (int u = 0; u < count; ++u) copies += std::equal(key.begin(), key.end(), dims + 3 * u);
+            if (!grouped) copies = 1;
             int rc = plan_create(&p, key[0], key[1], key[2], MIFFT_C2C, prec, flags & MIFFT_TUNE,
                                  std::min(copies, kMaxGroup));
             if (rc) {
@@ -717,6 +718,12 @@ int batch_describe(mifft_batch b, char* buf, size_t len)
         snprintf(line, sizeof(line), "mode=%s transforms=%d shapes=%zu\n", b->grouped ? "grouped" : "kernels",
                  b->count, b->plans.size());
         s += line;
+        for (const auto& kv : b->plans) {
+            const Plan* P = plan_of(kv.second);
+            snprintf(line, sizeof(line), "shape=%dx%dx%d launched_together=%d passes=%zu\n", kv.first[0], kv.first[1],
+                     kv.first[2], P->copies, P->exec_fwd().size());
+            s += line;
+        }
     } else {
         snprintf(line, sizeof(line), "mode=persistent transforms=%d passes=%zu items=%d grid=%u block=%d lds=%zu\n",
                  b->count, b->passes.size(), b->total_items, b->grid, kBatchBlock, b->lds);

@@ -2264,6 +2264,7 @@ int build_planes(Plan& plan)
         if (atoi(e) == 0) return MIFFT_OK;
     if (getenv("MIFFT_CHUNK_MIB") || getenv("MIFFT_BLOCKED")) return MIFFT_OK;
     if (plan.pencil || plan.slab) return MIFFT_OK;
+    if (plan.ws_bytes) plan.copies = 1; // transforms that share a workspace are launched one by one
     int rc;
     bool fused = false;
     std::vector<Pass> f = plan.fwd, v = plan.inv, po = plan.poisson;

@@ -154,7 +154,7 @@ public:
     int slab_p = 1;
     // arrays of rank > 3 (Algorithm 2): the extents, first (slowest) to last;
     // n0 n1 n2 then hold (product of the leading extents, second-to-last, last)
-    int copies = 1; // transforms of this shape that a batch launches together
+    int copies = 1; // transforms of this shape that a grouped batch launches together
     bool nd = false;
     std::vector<int> dims;
     Pass sz, sy, sy_pack, spk, sx, sxi, supk, syi, syi_unpack, szi;

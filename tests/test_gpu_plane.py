@@ -263,3 +263,23 @@ def test_in_place_split_calls_agree_bit_for_bit(monkeypatch, split, shape, prec)
         b.forward(xs, [xs[0], torch.empty_like(x2), xs[2]])
         assert torch.equal(xs[0], ref[0]) and torch.equal(xs[2], ref[2]) and torch.equal(xs[1], x2)
         b.close()
+
+
+@pytest.mark.parametrize("mode,shape,together", [("kernels", (64, 128, 128), 1), ("grouped", (64, 128, 128), 4),
+                                                 ("grouped", (4, 256, 128), 1), ("kernels", (4, 256, 128), 1)])
+def test_schedules_count_only_what_runs_together(mode, shape, together):
+    """The planner chooses for the tiles of one launch: a batch of per-pass
+    kernels, and transforms that need a workspace, run one by one."""
+    from paper_1506_07933_amd import BatchPlan, Plan
+    xs = [torch.from_numpy(synth.uniform_complex(shape, np.complex64, seed=i)).cuda() for i in range(4)]
+    b = BatchPlan([shape] * 4, "fp32", mode=mode)
+    assert "shape=%dx%dx%d launched_together=%d " % (*shape, together) in b.describe()
+    outs = b.forward(xs)
+    p = Plan(shape, "c2c", "fp32")
+    for x, o in zip(xs, outs):
+        if together == 1:
+            assert torch.equal(o, p.forward(x))
+        else:
+            assert rel_l2(o.cpu().numpy(), oracle.fft3d_c2c(x.cpu().numpy().astype(np.complex128), -1)) <= TOL["fp32"]
+    p.close()
+    b.close()
