@@ -72,7 +72,7 @@ class BatchPlan:
         return bool(flag.value)
 
     def describe(self) -> str:
-        buf = ctypes.create_string_buffer(4096)
+        buf = ctypes.create_string_buffer(1 << 16)
         check(lib.mifft_batch_describe(self.handle, buf, len(buf)), "mifft_batch_describe")
         return buf.value.decode()
 

@@ -728,9 +728,17 @@ int batch_describe(mifft_batch b, char* buf, size_t len)
         snprintf(line, sizeof(line), "mode=persistent transforms=%d passes=%zu items=%d grid=%u block=%d lds=%zu\n",
                  b->count, b->passes.size(), b->total_items, b->grid, kBatchBlock, b->lds);
         s += line;
-        // one line per (stage, length): the code path and item size in use
-        std::map<std::pair<int, int>, const BatchPass*> seen;
-        for (const BatchPass& p : b->passes) seen.emplace(std::make_pair(p.stage, p.L), &p);
+        // one line per (stage, length): the code path and item size in use; one
+        // per plane shape
+        std::map<std::pair<int, int>, const BatchPass*> seen, planes;
+        for (const BatchPass& p : b->passes)
+            (p.kind == 2 ? planes : seen).emplace(std::make_pair(p.kind == 2 ? p.cp.A : p.stage, p.L), &p);
+        for (const auto& kv : planes) {
+            const BatchPass& p = *kv.second;
+            snprintf(line, sizeof(line), "stage=zy L=%d rows=%d tpl=%d sub_per_item=%d\n", p.L, p.cp.A, p.tpl,
+                     p.sub_per_item);
+            s += line;
+        }
         for (const auto& kv : seen) {
             const BatchPass& p = *kv.second;
             const int var = p.code % kBatchVariants;

@@ -283,3 +283,19 @@ def test_schedules_count_only_what_runs_together(mode, shape, together):
             assert rel_l2(o.cpu().numpy(), oracle.fft3d_c2c(x.cpu().numpy().astype(np.complex128), -1)) <= TOL["fp32"]
     p.close()
     b.close()
+
+
+def test_batch_report_tells_plane_items_from_lines():
+    """A plane pass and a z-pass of one length: both are listed, as what they are."""
+    from paper_1506_07933_amd import BatchPlan
+    shapes = [(40, 4, 100), (2, 125, 100), (6, 240, 100), (3, 256, 250)]
+    b = BatchPlan(shapes, "fp64")
+    lines = [dict(kv.split("=") for kv in line.split() if "=" in kv) for line in b.describe().splitlines()
+             if line.startswith("stage=")]
+    assert len([1 for d in lines if d["stage"] == "zy"]) == 1
+    assert [(d["L"], d["rows"]) for d in lines if d["stage"] == "zy"] == [("100", "4")]
+    assert sorted(int(d["L"]) for d in lines if d["stage"] == "z") == [100, 250]
+    assert sorted(int(d["L"]) for d in lines if d["stage"] == "y") == [125, 240, 256]
+    assert sorted(int(d["L"]) for d in lines if d["stage"] == "x") == [2, 3, 6, 40]
+    assert all(d["policy"] in ("0", "2") and d["emul"] in ("1", "2") for d in lines if d["stage"] != "zy")
+    b.close()
