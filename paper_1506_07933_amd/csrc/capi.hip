@@ -916,13 +916,13 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
                  "%s kind=%s axis=%c L=%d policy=%d tpl=%d sgn=%d lines=%lld lpw=%d B=%d cols=%d groups=%d "
                  "es=%lld/%lld gs=%lld/%lld off=%lld/%lld grid=%u block=%u lds=%zu pf=%d tpg=%d tiles=%d nt=%d "
                  "nto=%d gdiv=%d/%d gs2=%lld/%lld pm=%u/%lld ni=%d is=%lld/%lld os=%lld/%lld lane=%d nb=%d C=%d "
-                 "rows=%d sb=%lld/%lld ys=%lld/%lld tw=%d buf=%s>%s%s%s\n",
+                 "rows=%d sb=%lld/%lld ys=%lld/%lld tw=%d xcd=%d buf=%s>%s%s%s\n",
                  tag, kn[q.kind], "zyx-"[q.tag < 3 ? q.tag : 3], q.L, pol, tpl, q.sgn, q.nlines, q.lines_per_wg,
                  q.B, q.cols, q.groups, q.es_in, q.es_out, q.gs_in, q.gs_out, q.off_in, q.off_out, q.grid,
                  q.block, q.shmem, pf, q.tpg, q.ntiles, q.nt_in, q.nt_out, q.gdiv_in, q.gdiv_out, q.gs2_in,
                  q.gs2_out, q.kind == mifft::P_CONTIG_PACK ? q.fd.d : 0u, q.kind == mifft::P_CONTIG_PACK ? q.blk : 0,
                  q.ni, q.is_o, q.is_i, q.os_o, q.os_i, q.lane, q.nb, q.split_C, q.cp ? q.cp->A : 0, q.is_b, q.os_b, q.ys_in,
-                 q.ys_out, q.split_tw, bn[q.src], bn[q.dst], q.fork_after ? " fork=1" : "",
+                 q.ys_out, q.split_tw, q.xcd, bn[q.src], bn[q.dst], q.fork_after ? " fork=1" : "",
                  q.join_before ? " join=1" : "");
         s += line;
     };

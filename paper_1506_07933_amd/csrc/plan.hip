@@ -535,7 +535,7 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         a.ys_out = (uint32_t)p.ys_out;
         a.sgn = (T)p.sgn;
         a.nt_out = p.nt_out;
-        a.xcd = p.ntiles % 8 == 0 && !getenv("MIFFT_NOXCD");
+        a.xcd = p.xcd;
         a.cp = *p.cp;
         const bool mid = p.kind == P_COLS_MID;
         ensure_lds(cols_kernel(sizeof(T) == 8, mid), p.shmem);
@@ -2170,6 +2170,7 @@ static int build_split(Plan& plan)
         c.tpg = (nc + sp.C - 1) / sp.C;
         c.ntiles = c.flat ? (int)(((long long)A * nc + sp.C - 1) / sp.C) : A * c.tpg;
         c.shmem = cols_lds(plan, B, sp.C);
+        c.xcd = c.ntiles % 8 == 0;
         c.block = (unsigned)cols_threads(plan, B, sp.C, (long long)A * nc / sp.C);
         const size_t out_bytes = (size_t)n0 * plane * plan.esz;
         a.nt_out = c2r && out_bytes >= ((size_t)128 << 20);
@@ -2241,6 +2242,7 @@ static int build_split_spectral(Plan& plan)
     c.tpg = (nc + sp.C - 1) / sp.C;
     c.ntiles = A * c.tpg;
     c.shmem = cols_lds(plan, B, sp.C);
+    c.xcd = c.ntiles % 8 == 0;
     c.block = (unsigned)cols_threads(plan, B, sp.C, c.ntiles);
     c.cus = plan.cus;
     c.grid = cols_grid(c, 1);

@@ -99,6 +99,7 @@ struct Pass {
     // split y-axis: plane tiles (x, b) of nb per x, rows b s_b apart; the
     // columns pass takes nb points of y1 and split_C columns of k2 per tile
     int nb = 1, split_C = 0, flat = 0;
+    int xcd = 0; // columns pass: each XCD takes a consecutive run of tiles (cols_locate)
     int need_waves = 0, cus = 256; // plane passes: wavefronts a tile can use
     int split_tw = 0; // results take the factors w_n1^{y1 ka}
     long long is_b = 0, os_b = 0, ys_in = 0, ys_out = 0;

@@ -210,3 +210,19 @@ def test_in_place_split_maps_use_the_callers_buffer_only(monkeypatch, split, sha
         _plane(plane, buf.copy(), buf, n1)
         _cols(cols, buf.copy(), buf, n1)
         assert np.linalg.norm(buf.reshape(shape) - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+def test_tile_order_is_the_plans():
+    """Which tiles an XCD takes is fixed when the plan is made (the environment
+    is not read at launch): consecutive ones where their number divides by 8."""
+    seen = set()
+    for shape, kind, prec in (((256, 256, 256), 1, 0), ((256, 256, 256), 1, 1), ((200, 20, 450), 0, 1), ((200, 200, 200), 0, 0)):
+        lists, _ = _lists(shape, kind, prec)
+        for name, passes in lists.items():
+            for p in passes:
+                if p["kind"] in ("cols", "cols_mid"):
+                    assert p["xcd"] == (p["tiles"] % 8 == 0), (shape, name)
+                    seen.add(p["xcd"])
+                else:
+                    assert p["xcd"] == 0
+    assert seen == {0, 1}
