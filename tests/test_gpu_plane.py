@@ -299,3 +299,108 @@ def test_batch_report_tells_plane_items_from_lines():
     assert sorted(int(d["L"]) for d in lines if d["stage"] == "x") == [2, 3, 6, 40]
     assert all(d["policy"] in ("0", "2") and d["emul"] in ("1", "2") for d in lines if d["stage"] != "zy")
     b.close()
+
+
+@pytest.mark.parametrize("split,shape,prec", [(None, (40, 48, 100), "fp32"), (None, (8, 6, 4), "fp64"), ("2,8", (6, 8, 60), "fp32"),
+                                              ("4,8", (16, 256, 128), "fp64"), ("6,8", (81, 24, 60), "fp32")])
+def test_spectral_operators_in_a_callers_workspace(monkeypatch, split, shape, prec):
+    """Workspaces of exactly the reported sizes: the bits of the plan's own, and
+    nothing written past their ends."""
+    from paper_1506_07933_amd import Plan
+    if split:
+        monkeypatch.setenv("MIFFT_SPLIT", split)
+    rd = np.float32 if prec == "fp32" else np.float64
+    f = torch.from_numpy(synth.normal_real(shape, rd, seed=5)).cuda()
+    v = [torch.from_numpy(synth.normal_real(shape, rd, seed=20 + j)).cuda() for j in range(3)]
+    p = Plan(shape, "r2c", prec)
+    assert _plane_lines(p, "poisson")
+
+    def guarded(nbytes):
+        t = torch.full((nbytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        return t, t[:nbytes]
+
+    full, ws = guarded(p.poisson_ws_bytes)
+    for op in range(6):
+        assert torch.equal(p.spectral(op, f, alpha=1.5, ws=ws), p.spectral(op, f, alpha=1.5))
+    assert bool((full[p.poisson_ws_bytes:] == 0x5A).all())
+    full, ws = guarded(p.spectral_ws_bytes)
+    for a, b in zip(p.gradient(f, ws=ws), p.gradient(f)):
+        assert torch.equal(a, b)
+    assert torch.equal(p.divergence(v, ws=ws), p.divergence(v))
+    assert bool((full[p.spectral_ws_bytes:] == 0x5A).all())
+    p.close()
+
+
+def _no_element_finite(t):
+    r = torch.view_as_real(t) if t.is_complex() else t.unsqueeze(-1)
+    return not bool(torch.isfinite(r).all(-1).any())
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("split,shape", [(None, (20, 36, 100)), (None, (3, 16, 30)), ("2,16", (6, 8, 12)), ("4,8", (40, 8, 20)),
+                                         ("4,8", (30, 256, 128)), ("5,8", (9, 100, 10))])
+def test_nan_and_infinity_reach_every_output(monkeypatch, split, shape, prec):
+    """Every output depends on every input: one NaN or infinity leaves no
+    element finite (no padding, idle lane or masked column takes its place)."""
+    from paper_1506_07933_amd import Plan
+    if split:
+        monkeypatch.setenv("MIFFT_SPLIT", split)
+    cd, rd = (np.complex64, np.float32) if prec == "fp32" else (np.complex128, np.float64)
+    at = tuple(n - 1 for n in shape)
+    for bad in (float("nan"), float("inf"), float("-inf")):
+        p = Plan(shape, "c2c", prec)
+        x = torch.from_numpy(synth.uniform_complex(shape, cd, seed=1)).cuda()
+        x[at] = complex(bad, 0.25)
+        assert _no_element_finite(p.forward(x)) and _no_element_finite(p.inverse(x))
+        z = x.clone()
+        assert _no_element_finite(p.forward(z, out=z))
+        p.close()
+        p = Plan(shape, "r2c", prec)
+        r = torch.from_numpy(synth.normal_real(shape, rd, seed=1)).cuda()
+        r[at] = bad
+        assert _no_element_finite(p.forward(r))
+        if bad != bad:
+            assert _no_element_finite(p.poisson(r))
+            assert all(_no_element_finite(g) for g in p.gradient(r))
+            h = p.forward(torch.from_numpy(synth.normal_real(shape, rd, seed=2)).cuda())
+            h[0, 0, 1] = complex(bad, bad)
+            assert _no_element_finite(p.inverse(h))
+        p.close()
+
+
+@pytest.mark.parametrize("mode", ["grouped", "persistent"])
+def test_nan_stays_in_its_transform(mode):
+    from paper_1506_07933_amd import BatchPlan
+    shapes = [(12, 20, 36)] * 5 + [(30, 64, 64)] * 2
+    xs = [torch.from_numpy(synth.uniform_complex(s, np.complex64, seed=i)).cuda() for i, s in enumerate(shapes)]
+    b = BatchPlan(shapes, "fp32", mode=mode)
+    want = b.forward(xs)
+    bad = [x.clone() for x in xs]
+    for k in (1, 6):
+        bad[k][3, 4, 5] = complex(float("nan"), 0.0)
+    got = b.forward(bad)
+    torch.cuda.synchronize()
+    assert mode == "grouped" or not b.aborted()
+    for k, (g, w) in enumerate(zip(got, want)):
+        assert _no_element_finite(g) if k in (1, 6) else torch.equal(g, w)
+    b.close()
+
+
+def test_first_call_of_a_plan_under_capture():
+    """A large-LDS kernel whose first launch is a capture: replays give the
+    eager result, with eager work between them."""
+    from paper_1506_07933_amd import Plan
+    p = Plan((300, 96, 90), "c2c", "fp64")
+    assert _plane_lines(p, "forward")
+    x = torch.from_numpy(synth.uniform_complex((300, 96, 90), np.complex128, seed=2)).cuda()
+    y = torch.zeros_like(x)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        p.forward(x, out=y)
+    for seed in (2, 3, 4):
+        x.copy_(torch.from_numpy(synth.uniform_complex((300, 96, 90), np.complex128, seed=seed)))
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, p.forward(x))
+    p.close()
