@@ -526,8 +526,7 @@ static bool list_groupable(const Plan& P, const std::vector<Pass>& list)
 {
     if (P.ws_bytes != 0) return false;
     for (const Pass& q : list)
-        if ((q.kind != P_CONTIG && q.kind != P_STRIDED && q.kind != P_PLANE && q.kind != P_COLS &&
-             q.kind != P_ROWS) ||
+        if ((q.kind != P_CONTIG && q.kind != P_STRIDED && q.kind != P_PLANE && q.kind != P_COLS) ||
             (q.src != B_IN && q.src != B_OUT) || (q.dst != B_IN && q.dst != B_OUT))
             return false;
     return true;
@@ -536,7 +535,7 @@ static bool list_groupable(const Plan& P, const std::vector<Pass>& list)
 static int enqueue_grouped(mifft_batch b, void* const* in, void* const* out, hipStream_t s)
 {
     // the transforms of one shape that run the same list: an in-place one may
-    // run another than the rest (Plan::plane_fwd_ip)
+    // run another than the rest (Plan::plane_oop)
     struct Group {
         mifft_plan plan;
         const std::vector<Pass>* list;
@@ -547,10 +546,10 @@ static int enqueue_grouped(mifft_batch b, void* const* in, void* const* out, hip
     size_t npass = 0;
     for (const auto& kv : b->plans) {
         const Plan* P = plan_of(kv.second);
-        Group g[2] = {{kv.second, &P->exec_fwd(), false, {}}, {kv.second, &P->plane_fwd_ip, false, {}}};
+        Group g[2] = {{kv.second, &P->exec_fwd(), false, {}}, {kv.second, &P->fwd, false, {}}};
         for (int t = 0; t < b->count; ++t)
             if (std::equal(kv.first.begin(), kv.first.end(), b->dims.begin() + 3 * t))
-                g[in[t] == out[t] && !P->plane_fwd_ip.empty()].members.push_back(t);
+                g[in[t] == out[t] && P->plane_oop].members.push_back(t);
         for (Group& k : g) {
             if (k.members.empty()) continue;
             k.together = list_groupable(*P, *k.list);

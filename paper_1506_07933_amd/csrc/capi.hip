@@ -503,18 +503,18 @@ static int check_exec(mifft_plan plan, const void* in, void* out, void* ws, bool
 }
 
 // The pass list of a call: plans with the blocked schedule run their
-// transposed-schedule lists when the call is in place (in == out), split
-// plans without a workspace their in-place ones.
-static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out)
+// transposed-schedule lists when the call is in place (in == out).
+// `own`: the call's workspace is the plan's own.
+static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out, bool own)
 {
     if (in != out) return p.exec_fwd();
-    if (!p.plane_fwd_ip.empty()) return p.plane_fwd_ip;
+    if (!p.plane_fwd_ip.empty()) return own ? p.plane_fwd_ip : p.fwd;
     return p.fwd_ip.empty() ? p.exec_fwd() : p.fwd_ip;
 }
-static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out)
+static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out, bool own)
 {
     if (in != out) return p.exec_inv();
-    if (!p.plane_inv_ip.empty()) return p.plane_inv_ip;
+    if (!p.plane_inv_ip.empty()) return own ? p.plane_inv_ip : p.inv;
     return p.inv_ip.empty() ? p.exec_inv() : p.inv_ip;
 }
 
@@ -523,7 +523,7 @@ int mifft_execute_forward_ws(mifft_plan plan, const void* in, void* out, void* w
     clear_error();
     int rc = check_exec(plan, in, out, ws, true);
     if (rc) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_inverse_ws(mifft_plan plan, const void* in, void* out, void* ws, void* stream)
@@ -531,7 +531,7 @@ int mifft_execute_inverse_ws(mifft_plan plan, const void* in, void* out, void* w
     clear_error();
     int rc = check_exec(plan, in, out, ws, true);
     if (rc) return rc;
-    return run_passes(*plan, inv_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, inv_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_forward(mifft_plan plan, const void* in, void* out, void* stream)
@@ -539,7 +539,7 @@ int mifft_execute_forward(mifft_plan plan, const void* in, void* out, void* stre
     clear_error();
     int rc = check_exec(plan, in, out, nullptr, false);
     if (rc) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out, true), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_inverse(mifft_plan plan, const void* in, void* out, void* stream)
@@ -547,7 +547,7 @@ int mifft_execute_inverse(mifft_plan plan, const void* in, void* out, void* stre
     clear_error();
     int rc = check_exec(plan, in, out, nullptr, false);
     if (rc) return rc;
-    return run_passes(*plan, inv_list(*plan, in, out), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, inv_list(*plan, in, out, true), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 // Forward transform whose workspace is the file-scope device array below
@@ -602,7 +602,7 @@ int mifft_execute_forward_static(mifft_plan plan, const void* in, void* out, voi
                          dev);
     void* ws = nullptr;
     if (plan->ws_bytes && (rc = scratch_address(dev, &ws))) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 static int check_spectral(mifft_plan plan, const void* ws)
@@ -852,7 +852,6 @@ int mifft_profile_begin(mifft_plan plan, int max_calls)
     if (max_calls < 1 || max_calls > 100000) return set_error(MIFFT_ERR_INVALID, "max_calls out of range");
     size_t longest = std::max(plan->fwd.size(), std::max(plan->inv.size(), plan->poisson.size()));
     longest = std::max(longest, std::max(plan->fwd_ip.size(), plan->inv_ip.size()));
-    longest = std::max(longest, std::max(plan->plane_fwd_ip.size(), plan->plane_inv_ip.size()));
     if (longest < 4) longest = 4; // stage calls of pencil and slab plans
     const int stride = (int)longest + 1;
     const size_t need = (size_t)max_calls * stride;
@@ -902,11 +901,10 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
     if (!is_live(plan)) return set_error(MIFFT_ERR_BADPLAN, "handle is not a live plan");
     static const char* kn[] = {"contig", "contig_pack", "strided", "strided_unpack", "r2c_z",
                                "c2r_z",  "poisson",     "pack",    "unpack",         "copy", "poisson_x",
-                               "strided_pack", "plane", "plane_r2c", "plane_c2r", "cols", "cols_mid", "rows"};
-    static const char* bn[] = {"-", "in", "out", "ws", "send", "recv"};
+                               "strided_pack", "plane", "plane_r2c", "plane_c2r", "cols", "cols_mid"};
     std::string s;
     auto add = [&](const char* tag, const Pass& q) {
-        char line[896];
+        char line[768];
         int pol = q.vidx >= 0 ? variant_policy(plan->prec, q.vidx) : -1;
         int tpl = q.vidx >= 0 ? variant_tpl(plan->prec, q.vidx) : 0;
         const bool strided = q.kind == mifft::P_STRIDED || q.kind == mifft::P_STRIDED_SPLIT ||
@@ -916,13 +914,13 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
                  "%s kind=%s axis=%c L=%d policy=%d tpl=%d sgn=%d lines=%lld lpw=%d B=%d cols=%d groups=%d "
                  "es=%lld/%lld gs=%lld/%lld off=%lld/%lld grid=%u block=%u lds=%zu pf=%d tpg=%d tiles=%d nt=%d "
                  "nto=%d gdiv=%d/%d gs2=%lld/%lld pm=%u/%lld ni=%d is=%lld/%lld os=%lld/%lld lane=%d nb=%d C=%d "
-                 "rows=%d sb=%lld/%lld ys=%lld/%lld tw=%d xcd=%d buf=%s>%s%s%s\n",
+                 "rows=%d sb=%lld/%lld ys=%lld/%lld tw=%d xcd=%d%s%s\n",
                  tag, kn[q.kind], "zyx-"[q.tag < 3 ? q.tag : 3], q.L, pol, tpl, q.sgn, q.nlines, q.lines_per_wg,
                  q.B, q.cols, q.groups, q.es_in, q.es_out, q.gs_in, q.gs_out, q.off_in, q.off_out, q.grid,
                  q.block, q.shmem, pf, q.tpg, q.ntiles, q.nt_in, q.nt_out, q.gdiv_in, q.gdiv_out, q.gs2_in,
                  q.gs2_out, q.kind == mifft::P_CONTIG_PACK ? q.fd.d : 0u, q.kind == mifft::P_CONTIG_PACK ? q.blk : 0,
                  q.ni, q.is_o, q.is_i, q.os_o, q.os_i, q.lane, q.nb, q.split_C, q.cp ? q.cp->A : 0, q.is_b, q.os_b, q.ys_in,
-                 q.ys_out, q.split_tw, q.xcd, bn[q.src], bn[q.dst], q.fork_after ? " fork=1" : "",
+                 q.ys_out, q.split_tw, q.xcd, q.fork_after ? " fork=1" : "",
                  q.join_before ? " join=1" : "");
         s += line;
     };
@@ -953,8 +951,6 @@ int mifft_plan_describe(mifft_plan plan, char* buf, size_t len)
         for (const Pass& q : plan->plane_fwd) add("plane_forward", q);
         for (const Pass& q : plan->plane_inv) add("plane_inverse", q);
         for (const Pass& q : plan->plane_poisson) add("plane_poisson", q);
-        for (const Pass& q : plan->plane_fwd_ip) add("plane_forward_inplace", q);
-        for (const Pass& q : plan->plane_inv_ip) add("plane_inverse_inplace", q);
     }
     snprintf(buf, len, "%s", s.c_str());
     return MIFFT_OK;

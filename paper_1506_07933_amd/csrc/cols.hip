@@ -22,22 +22,6 @@ hipError_t launch_cols(const ColsArgs<double>& a, dim3 grid, unsigned block, siz
     return hipGetLastError();
 }
 
-const void* rows_kernel(bool fp64)
-{
-    return fp64 ? reinterpret_cast<const void*>(&k_rows<double>) : reinterpret_cast<const void*>(&k_rows<float>);
-}
-
-hipError_t launch_rows(const RowsArgs<float>& a, dim3 grid, size_t lds, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_rows<float>, grid, dim3(kRowsBlock), lds, s, a);
-    return hipGetLastError();
-}
-hipError_t launch_rows(const RowsArgs<double>& a, dim3 grid, size_t lds, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_rows<double>, grid, dim3(kRowsBlock), lds, s, a);
-    return hipGetLastError();
-}
-
 hipError_t launch_cols_mid(const MidArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s)
 {
     hipLaunchKernelGGL(k_cols_mid<float>, grid, dim3(block), lds, s, a);

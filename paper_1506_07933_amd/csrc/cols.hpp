@@ -34,8 +34,6 @@ constexpr int cols_pitch(int B, int C, int esz)
     return B * C + (esz == 8 && B * C % 32 == 0 && C <= 8 ? 4 : 0);
 }
 
-constexpr int kRowsBlock = 256; // k_rows
-
 template <typename T> struct ColsArgs {
     const cx<T>* in;
     cx<T>* out;
@@ -187,52 +185,6 @@ __device__ __forceinline__ void cols_stage(const ColsCtx<T>& x, const ColsArgs<T
             for (int r = 1; r < R; ++r) v[r] = cmul(v[r], *(w2 += e));
 #pragma unroll
             for (int r = 0; r < R; ++r) p[r * q * x.pitch] = v[r];
-        }
-    }
-}
-
-// ------------------------------------------------------- in-place calls
-// An in-place split transform without a workspace: its plane tiles would write
-// to rows that other tiles have yet to read.  The rows of each (g) plane first
-// move from y1 + B y2 to y1 A + y2, in place; plane tiles then read and write
-// the same A adjacent rows, and the columns pass is in place as it is, so the
-// three passes give the bits of the out-of-place two.  A tile is C columns of
-// one plane, all of it in LDS between the barrier's two sides.
-// What bounds it: a copy through the caches.
-template <typename T> struct RowsArgs {
-    const cx<T>* in;
-    cx<T>* out;
-    GroupPtrs<T> grp; // grouped launches, as in ContigArgs
-    int A, B;         // A B rows of `cols` elements
-    int cols, C, tpg; // columns of a tile, tiles per plane
-};
-
-template <typename T> __global__ __launch_bounds__(kRowsBlock) void k_rows(RowsArgs<T> a)
-{
-    using V = cx<T>;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    V* tile = reinterpret_cast<V*>(smem_raw);
-    const V* in = a.in;
-    V* out = a.out;
-    if (gridDim.y > 1) {
-        in = a.grp.in[blockIdx.y];
-        out = a.grp.out[blockIdx.y];
-    }
-    const int n1 = a.A * a.B, g = blockIdx.x / a.tpg;
-    const int c = threadIdx.x % a.C, y0 = threadIdx.x / a.C, ys = kRowsBlock / a.C;
-    const int col = (blockIdx.x - g * a.tpg) * a.C + c;
-    const bool valid = col < a.cols;
-    const long long base = (long long)g * n1 * a.cols + col;
-    if (valid) {
-#pragma unroll 8
-        for (int y = y0; y < n1; y += ys) tile[y * a.C + c] = in[base + (long long)y * a.cols];
-    }
-    __syncthreads();
-    if (valid) {
-#pragma unroll 4
-        for (int y = y0; y < n1; y += ys) {
-            const int y1 = y / a.A;
-            out[base + (long long)y * a.cols] = tile[((y - y1 * a.A) * a.B + y1) * a.C + c];
         }
     }
 }

@@ -551,22 +551,6 @@ static hipError_t launch_fft(const Pass& p, const void* src, void* dst, hipStrea
         }
         return launch_cols(a, dim3(ng > 1 ? cols_grid(p, ng) : p.grid, ng), p.block, p.shmem, s);
     }
-    case P_ROWS: {
-        RowsArgs<T> a{};
-        a.in = (const V*)src;
-        a.out = (V*)dst;
-        for (int i = 0; i < ng && ng > 1; ++i) {
-            a.grp.in[i] = (const V*)gsrc[i];
-            a.grp.out[i] = (V*)gdst[i];
-        }
-        a.A = p.L / p.nb;
-        a.B = p.nb;
-        a.cols = p.cols;
-        a.C = p.split_C;
-        a.tpg = p.tpg;
-        ensure_lds(rows_kernel(sizeof(T) == 8), p.shmem);
-        return launch_rows(a, dim3(p.grid, ng), p.shmem, s);
-    }
     case P_POISSON:
         return launch_spectral<T>((const V*)src, (V*)dst, p.n0, p.n1, p.n2c, p.nz, p.op, (T)p.scale, (T)p.alpha,
                                   p.acc, s);
@@ -584,7 +568,7 @@ hipError_t launch_pass_group(const Pass& p, int prec, int ng, const void* const*
                              hipStream_t s)
 {
     if (ng < 1 || ng > kMaxGroup || (p.kind != P_CONTIG && p.kind != P_STRIDED && p.kind != P_PLANE &&
-                                           p.kind != P_COLS && p.kind != P_ROWS))
+                                           p.kind != P_COLS))
         return hipErrorInvalidValue;
     if (prec == MIFFT_FP64) return launch_fft<double>(p, src[0], dst[0], s, ng, src, dst);
     return launch_fft<float>(p, src[0], dst[0], s, ng, src, dst);
@@ -1223,9 +1207,6 @@ Extent pass_extent(const Pass& p, size_t esz)
         e.out = oo + g * p.gs_out + x * p.es_out + y * p.ys_out + p.cols;
         break;
     }
-    case P_ROWS:
-        e.in = e.out = (p.groups - 1) * p.gs_in + (long long)(p.L - 1) * p.es_in + p.cols;
-        break;
     case P_POISSON:
         e.in = e.out = (long long)p.n0 * p.n1 * p.n2c;
         break;
@@ -1277,7 +1258,7 @@ int validate_extents(const Plan& plan)
     const long long half = (long long)plan.n0 * plan.n1 * (plan.n2 / 2 + 1);
     const long long sig = real ? N / 2 : N;   // signal side, complex units
     const long long spec = real ? half : N;   // spectrum side
-    const long long ws = (long long)(plan.ws_bytes / esz);
+    const long long ws = (long long)(plan.ws_bytes / esz), own = (long long)(plan.default_ws_bytes / esz);
     const long long pw = (long long)(plan.poisson_ws_bytes / 2 / esz);
     struct List {
         const std::vector<Pass>* v;
@@ -1293,10 +1274,11 @@ int validate_extents(const Plan& plan)
         for (size_t k = 0; k < l.v->size(); ++k) {
             const Pass& p = (*l.v)[k];
             const Extent e = pass_extent(p, plan.esz);
+            const bool ip = l.v == &plan.plane_fwd_ip || l.v == &plan.plane_inv_ip;
             const bool chain = l.v == &plan.plane_poisson && plan.spec_bytes; // one spectrum, in both halves
             auto cap = [&](BufId b) -> long long {
                 if (chain && b == B_SEND) return std::min(2 * pw, (long long)(plan.spec_bytes / esz));
-                return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? ws : (b == B_SEND || b == B_RECV) ? pw : 0;
+                return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? (ip ? own : ws) : (b == B_SEND || b == B_RECV) ? pw : 0;
             };
             if ((p.src != B_NONE && e.in > cap(p.src)) || (p.dst != B_NONE && e.out > cap(p.dst)))
                 return set_error(MIFFT_ERR_INVALID,
@@ -2039,37 +2021,11 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
     return found;
 }
 
-// The pass that moves row y1 + B y2 of every plane to y1 A + y2, in place:
-// tiles of 256-byte rows, half as wide while the n1 of them take more than 64 KiB.
-static Pass make_rows(const Plan& plan, int B)
-{
-    Pass p;
-    int row = 256;
-    while (row > 64 && (size_t)plan.n1 * row > kLdsBudget) row /= 2;
-    p.kind = P_ROWS;
-    p.src = B_IN;
-    p.dst = B_OUT;
-    p.tag = 3;
-    p.L = plan.n1;
-    p.nb = B;
-    p.split_C = row / (int)plan.esz;
-    p.cols = plan.n2;
-    p.groups = plan.n0;
-    p.es_in = p.es_out = plan.n2;
-    p.gs_in = p.gs_out = (long long)plan.n1 * plan.n2;
-    p.tpg = (p.cols + p.split_C - 1) / p.split_C;
-    p.ntiles = p.groups * p.tpg;
-    p.grid = (unsigned)p.ntiles;
-    p.block = kRowsBlock;
-    p.shmem = (size_t)plan.n1 * row;
-    return p;
-}
-
 // The plane pass (x, y1) over z and y2 and the columns pass over y1 and x.
 // With the transposed intermediate's workspace: W[ka][x][y1][k2] forward,
 // W[x][y1][ka][k2] for C2R.  Plans without it go through the output, ka at
-// row ka + A y1 (the columns pass then works in place); an in-place call of
-// theirs moves the rows first (k_rows), so that the plane pass is in place too.
+// row ka + A y1 (the columns pass then works in place); an in-place call runs
+// the same passes through the plan's own workspace, which gives the same bits.
 // Their C2R has a workspace of the half spectrum.
 static int build_split(Plan& plan)
 {
@@ -2133,6 +2089,7 @@ static int build_split(Plan& plan)
             a.os_o = W ? (long long)B * ncw : plane;
             a.os_b = W ? ncw : (long long)A * nc;
             if (!W) a.dst = B_OUT;
+            if (!W && !real) plan.plane_oop = true;
             c.src = a.dst;
             c.dst = B_OUT;
             c.gs_in = a.os_i;
@@ -2178,13 +2135,13 @@ static int build_split(Plan& plan)
         c.cus = plan.cus;
         c.grid = cols_grid(c, 1);
         (dir ? plan.plane_inv : plan.plane_fwd) = c2r ? std::vector<Pass>{c, a} : std::vector<Pass>{a, c};
-        if (!W && !real) {
-            const Pass r = make_rows(plan, B);
-            a.src = B_OUT;
-            a.is_i = a.os_i;
-            a.is_b = a.os_b;
-            a.is_o = a.os_o;
-            (dir ? plan.plane_inv_ip : plan.plane_fwd_ip) = {r, a, c};
+        if (plan.plane_oop) {
+            a.dst = c.src = B_WS;
+            a.os_i = c.gs_in = (long long)n0 * B * nc;
+            a.os_o = c.es_in = (long long)B * nc;
+            a.os_b = c.ys_in = nc;
+            (dir ? plan.plane_inv_ip : plan.plane_fwd_ip) = {a, c};
+            plan.default_ws_bytes = std::max(plan.default_ws_bytes, out_bytes);
         }
     }
     return MIFFT_OK;
@@ -2259,6 +2216,7 @@ int build_planes(Plan& plan)
     plan.plane_poisson.clear();
     plan.plane_mul = -1;
     plan.spec_bytes = 0;
+    plan.plane_oop = false;
     plan.plane_fwd_ip.clear();
     plan.plane_inv_ip.clear();
     // MIFFT_PLANES=0 and an explicit choice among the one-axis schedules keep those

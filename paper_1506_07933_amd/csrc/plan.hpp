@@ -34,8 +34,7 @@ enum PassKind {
     P_PLANE_R2C,
     P_PLANE_C2R,
     P_COLS,           // y1 and x of a split y-axis (cols.hpp)
-    P_COLS_MID,       // those of a spectral operator: forward, multiply, inverse
-    P_ROWS            // rows y1 + B y2 of every plane to y1 A + y2 (in-place calls)
+    P_COLS_MID        // those of a spectral operator: forward, multiply, inverse
 };
 
 // Which caller buffer a pass reads or writes; resolved at execute time.
@@ -137,8 +136,10 @@ public:
     // split spectral chain: its spectra (of spec_bytes, from the start of the
     // workspace on) take the place of the halves; 0: not split
     size_t spec_bytes = 0;
-    // plane_fwd / plane_inv of a C2C plan without a workspace run out of place
-    // only; in place these run: the rows moved first, then the same two passes
+    // plane_fwd / plane_inv of a C2C plan run out of place only; in place the
+    // same passes go through the plan's own workspace (these lists), or, in
+    // calls that bring their own (of ws_bytes, which is 0), fwd / inv run
+    bool plane_oop = false;
     std::vector<Pass> plane_fwd_ip, plane_inv_ip;
     const std::vector<Pass>& exec_fwd() const { return plane_fwd.empty() ? fwd : plane_fwd; }
     const std::vector<Pass>& exec_inv() const { return plane_inv.empty() ? inv : plane_inv; }
@@ -268,8 +269,5 @@ hipError_t launch_cols_mid(const MidArgs<float>& a, dim3 grid, unsigned block, s
 hipError_t launch_cols_mid(const MidArgs<double>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
 hipError_t launch_cols(const ColsArgs<float>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
 hipError_t launch_cols(const ColsArgs<double>& a, dim3 grid, unsigned block, size_t lds, hipStream_t s);
-const void* rows_kernel(bool fp64);
-hipError_t launch_rows(const RowsArgs<float>& a, dim3 grid, size_t lds, hipStream_t s);
-hipError_t launch_rows(const RowsArgs<double>& a, dim3 grid, size_t lds, hipStream_t s);
 
 } // namespace mifft

@@ -216,55 +216,6 @@ def test_persistent_plane_items(prec):
     b.close()
 
 
-@pytest.mark.parametrize("split,shape,prec", [(None, (100, 120, 144), "fp32"), (None, (5, 125, 100), "fp64"),
-                                              ("3,16", (5, 12, 18), "fp32"), ("8,8", (125, 32, 6), "fp64"),
-                                              ("4,8", (2, 1000, 6), "fp64"), ("5,8", (3, 100, 10), "fp32")])
-def test_in_place_split_calls_agree_bit_for_bit(monkeypatch, split, shape, prec):
-    """In place: the plain call, the one with a workspace, the static one and a
-    grouped batch's members give the bits of the out-of-place call, and calls
-    on two streams do not meet (the plan asks for no workspace and has none)."""
-    from paper_1506_07933_amd import BatchPlan, Plan
-    from paper_1506_07933_amd._lib import check, lib
-    if split:
-        monkeypatch.setenv("MIFFT_SPLIT", split)
-    cd = np.complex64 if prec == "fp32" else np.complex128
-    x = torch.from_numpy(synth.uniform_complex(shape, cd, seed=3)).cuda()
-    x2 = torch.from_numpy(synth.uniform_complex(shape, cd, seed=4)).cuda()
-    p = Plan(shape, "c2c", prec)
-    assert p.workspace_bytes == 0 and any("kind=rows" in line for line in _plane_lines(p, "forward_inplace"))
-    X, X2 = p.forward(x), p.forward(x2)
-    Y = p.inverse(X)
-    assert rel_l2(X.cpu().numpy(), oracle.fftnd_c2c(x.cpu().numpy().astype(np.complex128), -1)) <= TOL[prec]
-    ws = torch.empty(16, dtype=torch.uint8, device="cuda")
-    for kw in ({}, {"ws": ws}):
-        z = x.clone()
-        assert torch.equal(p.forward(z, out=z, **kw), X)
-        assert torch.equal(p.inverse(z, out=z, **kw), Y)
-    z = x.clone()
-    s = torch.cuda.current_stream().cuda_stream or None
-    check(lib.mifft_execute_forward_static(p.handle, z.data_ptr(), z.data_ptr(), s), "static")
-    assert torch.equal(z, X)
-    za, zb = x.clone(), x2.clone()
-    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
-    torch.cuda.synchronize()
-    for _ in range(8):
-        za.copy_(x)
-        zb.copy_(x2)
-        torch.cuda.synchronize()
-        p.forward(za, out=za, stream=sa)
-        p.forward(zb, out=zb, stream=sb)
-        torch.cuda.synchronize()
-        assert torch.equal(za, X) and torch.equal(zb, X2)
-    p.close()
-    for mode in ("grouped", "kernels"):
-        b = BatchPlan([shape] * 3, prec, mode=mode)
-        ref = b.forward([x, x2, x])
-        xs = [x.clone(), x2.clone(), x.clone()]
-        b.forward(xs, [xs[0], torch.empty_like(x2), xs[2]])
-        assert torch.equal(xs[0], ref[0]) and torch.equal(xs[2], ref[2]) and torch.equal(xs[1], x2)
-        b.close()
-
-
 @pytest.mark.parametrize("mode,shape,together", [("kernels", (64, 128, 128), 1), ("grouped", (64, 128, 128), 4),
                                                  ("grouped", (4, 256, 128), 1), ("kernels", (4, 256, 128), 1)])
 def test_schedules_count_only_what_runs_together(mode, shape, together):

@@ -176,42 +176,6 @@ def test_split_spectral_maps(monkeypatch, split, shape):
     assert np.linalg.norm(out - want) <= 1e-12 * np.linalg.norm(want)
 
 
-IN_PLACE = [(None, (100, 120, 144), 0), (None, (5, 125, 100), 1), ("2,16", (6, 8, 12), 1), ("3,16", (5, 12, 16), 0),
-            ("5,8", (3, 20, 10), 1), ("8,8", (5, 32, 6), 0), ("4,8", (2, 1000, 6), 1)]
-
-
-@pytest.mark.parametrize("split,shape,prec", IN_PLACE)
-def test_in_place_split_maps_use_the_callers_buffer_only(monkeypatch, split, shape, prec):
-    """A plan that asks for no workspace uses none in place either (calls on
-    several streams would share it): rows moved, then the plane and the columns
-    pass on the caller's buffer, each tile's outputs in its own inputs' places."""
-    if split:
-        monkeypatch.setenv("MIFFT_SPLIT", split)
-    n0, n1, n2 = shape
-    lists, ws = _lists(shape, 0, prec)
-    assert ws == 0
-    assert [p["kind"] for p in lists["plane_forward"]] == ["plane", "cols"]
-    rng = np.random.default_rng(11)
-    x = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
-    for name, ref in (("plane_forward_inplace", np.fft.fftn(x)), ("plane_inverse_inplace", np.fft.ifftn(x) * x.size)):
-        rows, plane, cols = lists[name]
-        assert [p["kind"] for p in lists[name]] == ["rows", "plane", "cols"]
-        assert {b for p in lists[name] for b in p["buf"].split(">")} <= {"in", "out"}
-        buf = x.reshape(-1).copy()
-        B = rows["nb"]
-        A = rows["L"] // B
-        assert (rows["L"], rows["cols"], rows["groups"]) == (n1, n2, n0)
-        assert rows["tpg"] * rows["C"] >= n2 and rows["tiles"] == n0 * rows["tpg"] == rows["grid"]
-        assert rows["lds"] >= n1 * rows["C"] * (16 if prec else 8) and rows["block"] % rows["C"] == 0
-        v = buf.reshape(n0, A, B, n2)  # row y1 + B y2
-        buf = np.ascontiguousarray(v.transpose(0, 2, 1, 3)).reshape(-1)  # to y1 A + y2
-        assert plane["is"] == plane["os"] and plane["sb"][0] == plane["sb"][1]
-        assert cols["gs"][0] == cols["gs"][1] and cols["es"][0] == cols["es"][1] and cols["ys"][0] == cols["ys"][1]
-        _plane(plane, buf.copy(), buf, n1)
-        _cols(cols, buf.copy(), buf, n1)
-        assert np.linalg.norm(buf.reshape(shape) - ref) <= 1e-12 * np.linalg.norm(ref)
-
-
 def test_tile_order_is_the_plans():
     """Which tiles an XCD takes is fixed when the plan is made (the environment
     is not read at launch): consecutive ones where their number divides by 8."""
