@@ -535,7 +535,7 @@ static bool list_groupable(const Plan& P, const std::vector<Pass>& list)
 static int enqueue_grouped(mifft_batch b, void* const* in, void* const* out, hipStream_t s)
 {
     // the transforms of one shape that run the same list: an in-place one may
-    // run another than the rest (Plan::plane_oop)
+    // run the one-axis passes (Plan::plane_oop)
     struct Group {
         mifft_plan plan;
         const std::vector<Pass>* list;

@@ -503,18 +503,18 @@ static int check_exec(mifft_plan plan, const void* in, void* out, void* ws, bool
 }
 
 // The pass list of a call: plans with the blocked schedule run their
-// transposed-schedule lists when the call is in place (in == out).
-// `own`: the call's workspace is the plan's own.
-static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out, bool own)
+// transposed-schedule lists when the call is in place (in == out), plans whose
+// split passes go through the output their one-axis lists.
+static const std::vector<Pass>& fwd_list(const Plan& p, const void* in, const void* out)
 {
     if (in != out) return p.exec_fwd();
-    if (!p.plane_fwd_ip.empty()) return own ? p.plane_fwd_ip : p.fwd;
+    if (p.plane_oop) return p.fwd;
     return p.fwd_ip.empty() ? p.exec_fwd() : p.fwd_ip;
 }
-static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out, bool own)
+static const std::vector<Pass>& inv_list(const Plan& p, const void* in, const void* out)
 {
     if (in != out) return p.exec_inv();
-    if (!p.plane_inv_ip.empty()) return own ? p.plane_inv_ip : p.inv;
+    if (p.plane_oop) return p.inv;
     return p.inv_ip.empty() ? p.exec_inv() : p.inv_ip;
 }
 
@@ -523,7 +523,7 @@ int mifft_execute_forward_ws(mifft_plan plan, const void* in, void* out, void* w
     clear_error();
     int rc = check_exec(plan, in, out, ws, true);
     if (rc) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_inverse_ws(mifft_plan plan, const void* in, void* out, void* ws, void* stream)
@@ -531,7 +531,7 @@ int mifft_execute_inverse_ws(mifft_plan plan, const void* in, void* out, void* w
     clear_error();
     int rc = check_exec(plan, in, out, ws, true);
     if (rc) return rc;
-    return run_passes(*plan, inv_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, inv_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_forward(mifft_plan plan, const void* in, void* out, void* stream)
@@ -539,7 +539,7 @@ int mifft_execute_forward(mifft_plan plan, const void* in, void* out, void* stre
     clear_error();
     int rc = check_exec(plan, in, out, nullptr, false);
     if (rc) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out, true), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int mifft_execute_inverse(mifft_plan plan, const void* in, void* out, void* stream)
@@ -547,7 +547,7 @@ int mifft_execute_inverse(mifft_plan plan, const void* in, void* out, void* stre
     clear_error();
     int rc = check_exec(plan, in, out, nullptr, false);
     if (rc) return rc;
-    return run_passes(*plan, inv_list(*plan, in, out, true), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, inv_list(*plan, in, out), in, out, plan->ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 // Forward transform whose workspace is the file-scope device array below
@@ -602,7 +602,7 @@ int mifft_execute_forward_static(mifft_plan plan, const void* in, void* out, voi
                          dev);
     void* ws = nullptr;
     if (plan->ws_bytes && (rc = scratch_address(dev, &ws))) return rc;
-    return run_passes(*plan, fwd_list(*plan, in, out, false), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
+    return run_passes(*plan, fwd_list(*plan, in, out), in, out, ws, nullptr, nullptr, (hipStream_t)stream);
 }
 
 static int check_spectral(mifft_plan plan, const void* ws)

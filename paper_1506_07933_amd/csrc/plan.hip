@@ -1258,7 +1258,7 @@ int validate_extents(const Plan& plan)
     const long long half = (long long)plan.n0 * plan.n1 * (plan.n2 / 2 + 1);
     const long long sig = real ? N / 2 : N;   // signal side, complex units
     const long long spec = real ? half : N;   // spectrum side
-    const long long ws = (long long)(plan.ws_bytes / esz), own = (long long)(plan.default_ws_bytes / esz);
+    const long long ws = (long long)(plan.ws_bytes / esz);
     const long long pw = (long long)(plan.poisson_ws_bytes / 2 / esz);
     struct List {
         const std::vector<Pass>* v;
@@ -1267,18 +1267,15 @@ int validate_extents(const Plan& plan)
     } lists[] = {{&plan.fwd, "forward", sig, spec},         {&plan.inv, "inverse", spec, sig},
                  {&plan.poisson, "poisson", sig, sig},         {&plan.fwd_ip, "in-place forward", sig, spec},
                  {&plan.inv_ip, "in-place inverse", spec, sig}, {&plan.plane_fwd, "plane forward", sig, spec},
-                 {&plan.plane_inv, "plane inverse", spec, sig}, {&plan.plane_poisson, "plane poisson", sig, sig},
-                 {&plan.plane_fwd_ip, "plane in-place forward", sig, spec},
-                 {&plan.plane_inv_ip, "plane in-place inverse", spec, sig}};
+                 {&plan.plane_inv, "plane inverse", spec, sig}, {&plan.plane_poisson, "plane poisson", sig, sig}};
     for (const List& l : lists) {
         for (size_t k = 0; k < l.v->size(); ++k) {
             const Pass& p = (*l.v)[k];
             const Extent e = pass_extent(p, plan.esz);
-            const bool ip = l.v == &plan.plane_fwd_ip || l.v == &plan.plane_inv_ip;
             const bool chain = l.v == &plan.plane_poisson && plan.spec_bytes; // one spectrum, in both halves
             auto cap = [&](BufId b) -> long long {
                 if (chain && b == B_SEND) return std::min(2 * pw, (long long)(plan.spec_bytes / esz));
-                return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? (ip ? own : ws) : (b == B_SEND || b == B_RECV) ? pw : 0;
+                return b == B_IN ? l.in : b == B_OUT ? l.out : b == B_WS ? ws : (b == B_SEND || b == B_RECV) ? pw : 0;
             };
             if ((p.src != B_NONE && e.in > cap(p.src)) || (p.dst != B_NONE && e.out > cap(p.dst)))
                 return set_error(MIFFT_ERR_INVALID,
@@ -2024,8 +2021,8 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
 // The plane pass (x, y1) over z and y2 and the columns pass over y1 and x.
 // With the transposed intermediate's workspace: W[ka][x][y1][k2] forward,
 // W[x][y1][ka][k2] for C2R.  Plans without it go through the output, ka at
-// row ka + A y1 (the columns pass then works in place); an in-place call runs
-// the same passes through the plan's own workspace, which gives the same bits.
+// row ka + A y1 (the columns pass then works in place); their in-place C2C
+// calls run the one-axis passes, which need no workspace either.
 // Their C2R has a workspace of the half spectrum.
 static int build_split(Plan& plan)
 {
@@ -2042,11 +2039,17 @@ static int build_split(Plan& plan)
     // 128^3 C2C FP32 24.3 us against 27.4, 128 x 128 x 64 FP64 24.3 against 26.8;
     // other lengths 100^3 24.7 against 20.7, 128 x 160 x 150 48.7 against 37.6, and
     // 128^3 FP64 R2C 35.7 against 29.3; a columns tile alone on its CU: 125^3 35.1
-    // against 37.8.
+    // against 37.8.  C2C calls in place run the one-axis passes, whose rounding
+    // differs: the split has to save more than launches for that, so not below
+    // 4 MiB (5 x 125 x 100 FP64 13.5 us against 12.7) and not where the columns
+    // pass leaves most of the device idle (64 x 96 x 128 FP32 18.5 against 18.8).
     auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
-    if (!W && !getenv("MIFFT_SPLIT") &&
-        (cols_threads(plan, B, sp.C, 1 << 20) > 512 || (!real && pow2(n1) && pow2(plan.n2))))
-        return MIFFT_OK;
+    if (!W && !getenv("MIFFT_SPLIT")) {
+        if (cols_threads(plan, B, sp.C, 1 << 20) > 512) return MIFFT_OK;
+        const long long bytes = (long long)n0 * n1 * nc * (long long)plan.esz;
+        if (!real && ((pow2(n1) && pow2(plan.n2)) || bytes < (4LL << 20) || 2LL * A * nc / sp.C < plan.cus))
+            return MIFFT_OK;
+    }
     const long long plane = (long long)n1 * nc;
     // 32-bit offsets inside a tile
     if ((unsigned long long)n0 * n1 * ncw * plan.esz >= (1ull << 32)) return MIFFT_OK;
@@ -2135,14 +2138,6 @@ static int build_split(Plan& plan)
         c.cus = plan.cus;
         c.grid = cols_grid(c, 1);
         (dir ? plan.plane_inv : plan.plane_fwd) = c2r ? std::vector<Pass>{c, a} : std::vector<Pass>{a, c};
-        if (plan.plane_oop) {
-            a.dst = c.src = B_WS;
-            a.os_i = c.gs_in = (long long)n0 * B * nc;
-            a.os_o = c.es_in = (long long)B * nc;
-            a.os_b = c.ys_in = nc;
-            (dir ? plan.plane_inv_ip : plan.plane_fwd_ip) = {a, c};
-            plan.default_ws_bytes = std::max(plan.default_ws_bytes, out_bytes);
-        }
     }
     return MIFFT_OK;
 }
@@ -2217,8 +2212,6 @@ int build_planes(Plan& plan)
     plan.plane_mul = -1;
     plan.spec_bytes = 0;
     plan.plane_oop = false;
-    plan.plane_fwd_ip.clear();
-    plan.plane_inv_ip.clear();
     // MIFFT_PLANES=0 and an explicit choice among the one-axis schedules keep those
     if (const char* e = getenv("MIFFT_PLANES"))
         if (atoi(e) == 0) return MIFFT_OK;

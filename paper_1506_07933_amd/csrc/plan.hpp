@@ -136,11 +136,9 @@ public:
     // split spectral chain: its spectra (of spec_bytes, from the start of the
     // workspace on) take the place of the halves; 0: not split
     size_t spec_bytes = 0;
-    // plane_fwd / plane_inv of a C2C plan run out of place only; in place the
-    // same passes go through the plan's own workspace (these lists), or, in
-    // calls that bring their own (of ws_bytes, which is 0), fwd / inv run
+    // plane_fwd / plane_inv run out of place only (they go through the output,
+    // tile by tile to rows that other tiles still read); in place fwd / inv run
     bool plane_oop = false;
-    std::vector<Pass> plane_fwd_ip, plane_inv_ip;
     const std::vector<Pass>& exec_fwd() const { return plane_fwd.empty() ? fwd : plane_fwd; }
     const std::vector<Pass>& exec_inv() const { return plane_inv.empty() ? inv : plane_inv; }
     const std::vector<Pass>& exec_poisson() const { return plane_poisson.empty() ? poisson : plane_poisson; }

@@ -355,3 +355,62 @@ def test_first_call_of_a_plan_under_capture():
         torch.cuda.synchronize()
         assert torch.equal(y, p.forward(x))
     p.close()
+
+
+@pytest.mark.parametrize("split,shape,prec", [(None, (100, 120, 144), "fp32"), (None, (100, 100, 100), "fp64"),
+                                              ("3,16", (50, 96, 90), "fp32"), ("8,8", (125, 32, 60), "fp64")])
+def test_in_place_split_calls_need_no_memory_and_agree(monkeypatch, split, shape, prec):
+    """A plan that reports no workspace has none: creating it takes less memory
+    than its array.  In place, the plain call, the one with a workspace, the
+    static one and the members of a batch give the same bits, also on two
+    streams at once; they run the one-axis passes, so the out-of-place call's
+    bits are near, not equal."""
+    from paper_1506_07933_amd import BatchPlan, Plan
+    from paper_1506_07933_amd._lib import check, lib
+    if split:
+        monkeypatch.setenv("MIFFT_SPLIT", split)
+    cd = np.complex64 if prec == "fp32" else np.complex128
+    x = torch.from_numpy(synth.uniform_complex(shape, cd, seed=3)).cuda()
+    x2 = torch.from_numpy(synth.uniform_complex(shape, cd, seed=4)).cuda()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    plans = [Plan(shape, "c2c", prec) for _ in range(4)]
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 4 * max(x.numel() * x.element_size() // 2, 2 << 20)
+    p = plans[0]
+    assert p.workspace_bytes == 0 and any("kind=cols" in line for line in _plane_lines(p, "forward"))
+    X = p.forward(x)
+    assert rel_l2(X.cpu().numpy(), oracle.fftnd_c2c(x.cpu().numpy().astype(np.complex128), -1)) <= TOL[prec]
+    z, z2 = x.clone(), x2.clone()
+    Z, Z2 = p.forward(z, out=z).clone(), p.forward(z2, out=z2).clone()
+    assert rel_l2(Z.cpu().numpy(), X.cpu().numpy()) <= TOL[prec]
+    Y = p.inverse(z, out=z).clone()
+    assert rel_l2(Y.cpu().numpy(), x.numel() * x.cpu().numpy().astype(np.complex128)) <= TOL[prec]
+    ws = torch.empty(16, dtype=torch.uint8, device="cuda")
+    z = x.clone()
+    assert torch.equal(p.forward(z, out=z, ws=ws), Z) and torch.equal(p.inverse(z, out=z, ws=ws), Y)
+    z = x.clone()
+    s = torch.cuda.current_stream().cuda_stream or None
+    check(lib.mifft_execute_forward_static(p.handle, z.data_ptr(), z.data_ptr(), s), "static")
+    assert torch.equal(z, Z)
+    za, zb = x.clone(), x2.clone()
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(8):
+        za.copy_(x)
+        zb.copy_(x2)
+        torch.cuda.synchronize()
+        p.forward(za, out=za, stream=sa)
+        p.forward(zb, out=zb, stream=sb)
+        torch.cuda.synchronize()
+        assert torch.equal(za, Z) and torch.equal(zb, Z2)
+    for q in plans:
+        q.close()
+    for mode in ("grouped", "kernels"):
+        b = BatchPlan([shape] * 3, prec, mode=mode)
+        xs = [x.clone(), x2.clone(), x.clone()]
+        b.forward(xs, [xs[0], torch.empty_like(x2), xs[2]])
+        assert torch.equal(xs[0], xs[2]) and torch.equal(xs[1], x2)
+        if mode == "kernels" or split:  # (grouped launches may choose another schedule for their tiles)
+            assert torch.equal(xs[0], Z)
+        assert rel_l2(xs[0].cpu().numpy(), X.cpu().numpy()) <= TOL[prec]
+        b.close()
