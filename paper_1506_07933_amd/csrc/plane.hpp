@@ -193,7 +193,8 @@ template <> struct Bfly<16> {
 // ------------------------------------------------------- radix choice
 
 // Radices of the z-lines and columns.  FP64 stops at 8: a butterfly's values,
-// its twiddles and the prefetched inputs have to fit 128 registers.
+// its twiddles and the prefetched inputs have to fit 128 registers (plane_line
+// leaves out the lengths that do not all the same).
 constexpr bool is_radix(int R, bool fp64)
 {
     return R == 2 || R == 3 || R == 4 || R == 5 || R == 6 || R == 8 ||
@@ -229,6 +230,18 @@ constexpr PlaneRadices plane_radices(int L, bool fp64)
     PlaneRadices cur{0, {}}, best{0, {}};
     plane_search(L, fp64, 16, L, cur, best);
     return best;
+}
+
+// z-lines that a plane kernel is compiled for.  FP64 lines of five stages, and of
+// four beyond 360 points, hold more than 128 registers beside the prefetched
+// rows (2 to 54 spilled) or pass the tile through LDS too often: 200 x 20 x 900 R2C 48
+// us as three passes, 60 as two; 300 x 9 x 480 C2C 40 against 47; 2 x 135 x 486 and the
+// like up to 1.5 times.  Four stages up to 360 points gain (360: 0.83 of the time).
+constexpr bool plane_line(int L, bool fp64)
+{
+    if (L < 2 || L > kMaxPlaneLine) return false;
+    const int n = plane_radices(L, fp64).n;
+    return !fp64 || n < 4 || (n == 4 && L <= 360);
 }
 
 // Threads per z-line: one first-stage butterfly each, or as many as keep the

@@ -30,7 +30,7 @@ template <typename T> struct Variant {
     RealFn<T> r2c; // line of 2L reals
     RealFn<T> c2r;
     PoissonXFn<T> poisson_x; // fused x-forward, multiply, x-inverse
-    // z- and y-axis in one pass, z-lines of L (policy 0, emul 1; else null)
+    // z- and y-axis in one pass, z-lines of L (policy 0, emul 1, plane_line; else null)
     PlaneFn<T> plane;
     PlaneFn<T> plane_r2c; // rows of 2L reals
     PlaneFn<T> plane_c2r;

@@ -35,7 +35,7 @@ template <int L, int P, int E> constexpr Variant<MIFFT_REAL> make_variant()
     v.c2r = &k_c2r_z<MIFFT_REAL, L, P, TPL>;
     v.poisson_x = &k_strided_poisson<MIFFT_REAL, L, P, TPL>;
     // one plane kernel per length, at its default variant
-    if constexpr (L >= 2 && L <= kMaxPlaneLine && P == 0 && E == 1) {
+    if constexpr (plane_line(L, sizeof(MIFFT_REAL) == 8) && P == 0 && E == 1) {
         v.plane = &k_plane<MIFFT_REAL, L>;
         v.plane_r2c = &k_plane_r2c<MIFFT_REAL, L>;
         v.plane_c2r = &k_plane_c2r<MIFFT_REAL, L>;

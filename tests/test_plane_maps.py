@@ -180,7 +180,7 @@ def test_tile_order_is_the_plans():
     """Which tiles an XCD takes is fixed when the plan is made (the environment
     is not read at launch): consecutive ones where their number divides by 8."""
     seen = set()
-    for shape, kind, prec in (((256, 256, 256), 1, 0), ((256, 256, 256), 1, 1), ((200, 20, 450), 0, 1), ((200, 200, 200), 0, 0)):
+    for shape, kind, prec in (((256, 256, 256), 1, 0), ((256, 256, 256), 1, 1), ((100, 120, 144), 0, 0), ((200, 200, 200), 0, 0)):
         lists, _ = _lists(shape, kind, prec)
         for name, passes in lists.items():
             for p in passes:
@@ -190,3 +190,14 @@ def test_tile_order_is_the_plans():
                 else:
                     assert p["xcd"] == 0
     assert seen == {0, 1}
+
+
+@pytest.mark.parametrize("shape,kind", [((200, 20, 900), 1), ((300, 9, 480), 0), ((200, 20, 972), 1), ((300, 9, 450), 0),
+                                        ((375, 30, 750), 1), ((120, 135, 486), 1), ((64, 10, 810), 1), ((200, 16, 500), 0)])
+def test_long_fp64_lines_keep_the_one_axis_passes(shape, kind):
+    """Lines whose plane kernels would not fit the registers, or take five
+    stages: the one-axis passes are faster."""
+    lists, _ = _lists(shape, kind, 1)
+    assert not [k for k in lists if k.startswith("plane_")]
+    lists, _ = _lists((200, 20, 720 if kind else 360), kind, 1)
+    assert lists["plane_forward"] and lists["plane_inverse"]
