@@ -1869,22 +1869,36 @@ static unsigned cols_grid(const Pass& p, int ng)
     return (unsigned)((p.ntiles + rounds - 1) / rounds);
 }
 
+// Whether `tiles` planes of this LDS pay, as a pass of their own (`split`: as
+// the first of a split y-axis).  A plane is one workgroup's work, however few
+// there are.  One that leaves no room for a second on its CU takes 11 us: it pays
+// only where such planes nearly fill the device (FP32, z and y apart against
+// fused, a whole transform: 64 x 128 x 128 18.5 against 22.0 us, 128 planes 24.6
+// against 26.2, 200 planes 39.6 against 36.1, 1024 planes 169 against 115), split
+// ones where they fill half of it (below: 2 x 243 x 180 14 against 23 us, 8 x 81 x
+// 864 R2C 16 against 22; on average 1.05 times the one-axis passes, above 0.83).
+// With a quarter of the device filled, smaller planes are too much work for
+// one workgroup as well, from 48 KiB on, or from 28 KiB where FP32 z-lines
+// take radices above 8 and so few threads (30 x 60 x 300 R2C 15 against 20 us, 12 x 20 x
+// 750 Poisson 22 against 27; above the lines on average 1.06 times, below 0.92;
+// 2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64 15.7 against 13.5).
+static bool plane_pays(const Plan& plan, int L, size_t lds, long long tiles, bool split)
+{
+    const long long t4 = 4 * tiles * plan.copies;
+    const bool wide = plan.prec == MIFFT_FP32 && radices_of(L, plan.prec).r[0] > 8;
+    return plan.plane_force || (!(2 * lds > kLdsMax && t4 < (split ? 2LL : 3LL) * plan.cus) &&
+                                !(lds > (wide ? 28 : 48) * 1024 && t4 < plan.cus));
+}
+
 // A plane pass of `tiles` planes of A rows from the z-pass (whose variant and
-// tables it takes); false where the plane does not fit.
+// tables it takes); false where the plane does not fit or does not pay.
 static int make_plane(Plan& plan, Pass& p, const Pass& z, int A, int tiles, bool split, bool* ok)
 {
     *ok = false;
     const size_t lds = plane_lds(plan, A, z.L);
     p.vidx = find_variant(plan.prec, z.L, 0, 1);
     if (p.vidx < 0 || A < 2 || lds > kLdsMax || !(p.cp = col_plan(plan, A))) return MIFFT_OK;
-    // A plane is one workgroup's work, and one that leaves no room for a second
-    // on its CU takes 11 us however few there are: those pay only where they
-    // nearly fill the device (FP32, z and y apart against fused, a whole
-    // transform: 64 x 128 x 128 18.5 against 22.0 us, 128 planes 24.6 against
-    // 26.2, 200 planes 39.6 against 36.1, 1024 planes 169 against 115).  Smaller
-    // planes pay at any count (2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64
-    // 15.7 against 13.5).
-    if (!split && 2 * lds > kLdsMax && 4LL * tiles * plan.copies < 3LL * plan.cus) return MIFFT_OK;
+    if (!split && !plane_pays(plan, z.L, lds, tiles, false)) return MIFFT_OK; // (choose_split has asked)
     p.kind = z.kind == P_R2C ? P_PLANE_R2C : z.kind == P_C2R ? P_PLANE_C2R : P_PLANE;
     p.L = z.L;
     if (!plane_fn(plan.prec, p)) return MIFFT_OK;
@@ -1995,13 +2009,19 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
     const double stages = radices_of(plan.n0, plan.prec).n > (plan.prec == MIFFT_FP64 ? 3 : 2) ? 1.1 : 1.0;
     size_t best_cl = 0;
     bool found = false;
+    // FP32 arrays below 2 MiB: launches only, 40 x 12 x 750 R2C 14.3 us against 16.1, Poisson 24.8
+    // against 28.9 (on average 0.98 and 0.99 times the one-axis passes, a third of them slower)
+    if (!fb && !plan.plane_force && plan.prec == MIFFT_FP32 &&
+        (long long)plan.n0 * plan.n1 * nc * (long long)plan.esz < (2LL << 20))
+        return false;
     for (int B : {2, 3, 4, 5, 6, 8}) {
         if (plan.n1 % B || plan.n1 / B < 2 || (fb && B != fb)) continue;
         const size_t pl = plane_lds(plan, plan.n1 / B, L);
+        if (pl > kLdsMax || (!fb && !plane_pays(plan, L, pl, (long long)plan.n0 * B, true))) continue;
         for (int C : {32, 16, 8, 4}) {
             const int row = C * (int)plan.esz;
             const size_t cl = cols_lds(plan, B, C);
-            if ((fc ? C != fc : row < 64 || row > 256) || pl > kLdsMax || cl > kLdsMax || !cols_threads(plan, B, C, (long long)plan.n1 / B * nc / C))
+            if ((fc ? C != fc : row < 64 || row > 256) || cl > kLdsMax || !cols_threads(plan, B, C, (long long)plan.n1 / B * nc / C))
                 continue;
             double rows = row >= 128 ? 1.0 : inner ? 1.2 : (size_t)nc * plan.esz % 128 == 0 ? 1.1 : 1.25;
             if (inner) rows *= (double)((nc + C - 1) / C * C) / nc;
@@ -2212,9 +2232,12 @@ int build_planes(Plan& plan)
     plan.plane_mul = -1;
     plan.spec_bytes = 0;
     plan.plane_oop = false;
+    plan.plane_force = false;
     // MIFFT_PLANES=0 and an explicit choice among the one-axis schedules keep those
-    if (const char* e = getenv("MIFFT_PLANES"))
+    if (const char* e = getenv("MIFFT_PLANES")) {
         if (atoi(e) == 0) return MIFFT_OK;
+        plan.plane_force = true; // planes wherever they fit
+    }
     if (getenv("MIFFT_CHUNK_MIB") || getenv("MIFFT_BLOCKED")) return MIFFT_OK;
     if (plan.pencil || plan.slab) return MIFFT_OK;
     if (plan.ws_bytes) plan.copies = 1; // transforms that share a workspace are launched one by one

@@ -139,6 +139,7 @@ public:
     // plane_fwd / plane_inv run out of place only (they go through the output,
     // tile by tile to rows that other tiles still read); in place fwd / inv run
     bool plane_oop = false;
+    bool plane_force = false; // MIFFT_PLANES=1: planes wherever they fit (comparison, tests)
     const std::vector<Pass>& exec_fwd() const { return plane_fwd.empty() ? fwd : plane_fwd; }
     const std::vector<Pass>& exec_inv() const { return plane_inv.empty() ? inv : plane_inv; }
     const std::vector<Pass>& exec_poisson() const { return plane_poisson.empty() ? poisson : plane_poisson; }

@@ -414,3 +414,31 @@ def test_in_place_split_calls_need_no_memory_and_agree(monkeypatch, split, shape
             assert torch.equal(xs[0], Z)
         assert rel_l2(xs[0].cpu().numpy(), X.cpu().numpy()) <= TOL[prec]
         b.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", [(5, 125, 100), (2, 250, 10), (3, 8, 512), (2, 18, 360), (3, 128, 128), (2, 81, 48),
+                                   (6, 96, 90), (2, 600, 5), (4, 108, 80), (3, 243, 54)])
+def test_planes_wherever_they_fit(monkeypatch, shape, prec):
+    """The schedules that the planner leaves out for speed (MIFFT_PLANES=1): near
+    the LDS limit, few planes, three and four stages."""
+    from paper_1506_07933_amd import Plan
+    monkeypatch.setenv("MIFFT_PLANES", "1")
+    cd, rd = (np.complex64, np.float32) if prec == "fp32" else (np.complex128, np.float64)
+    x = synth.uniform_complex(shape, cd, seed=sum(shape))
+    p = Plan(shape, "c2c", prec)
+    assert _plane_lines(p, "forward") and _plane_lines(p, "inverse")
+    X = p.forward(torch.from_numpy(x).cuda())
+    assert rel_l2(X.cpu().numpy(), oracle.fftnd_c2c(x.astype(np.complex128), -1)) <= TOL[prec]
+    assert rel_l2(p.inverse(X).cpu().numpy(), np.prod(shape) * x.astype(np.complex128)) <= TOL[prec]
+    p.close()
+    real = shape[:2] + (2 * shape[2],)
+    if real[2] > 1024:
+        return
+    p = Plan(real, "r2c", prec)
+    assert _plane_lines(p, "forward") and _plane_lines(p, "inverse")
+    r = synth.normal_real(real, rd, seed=3)
+    Y = p.forward(torch.from_numpy(r).cuda())
+    assert rel_l2(Y.cpu().numpy(), oracle.fftnd_r2c(r.astype(np.float64))) <= TOL[prec]
+    assert rel_l2(p.inverse(Y).cpu().numpy(), np.prod(real) * r.astype(np.float64)) <= TOL[prec]
+    p.close()

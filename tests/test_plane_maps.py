@@ -201,3 +201,21 @@ def test_long_fp64_lines_keep_the_one_axis_passes(shape, kind):
     assert not [k for k in lists if k.startswith("plane_")]
     lists, _ = _lists((200, 20, 720 if kind else 360), kind, 1)
     assert lists["plane_forward"] and lists["plane_inverse"]
+
+
+@pytest.mark.parametrize("shape,kind,prec", [((24, 60, 300), 1, 0), ((10, 45, 300), 1, 0), ((12, 20, 750), 1, 0), ((8, 108, 60), 0, 0),
+                                             ((2, 243, 180), 0, 0), ((3, 243, 162), 1, 1), ((8, 256, 256), 0, 1),
+                                             ((8, 81, 864), 1, 0), ((4, 600, 240), 0, 0), ((40, 12, 750), 1, 0)])
+def test_few_large_planes_keep_the_one_axis_passes(monkeypatch, shape, kind, prec):
+    """A plane is one workgroup's work: few and large ones are slower than the
+    separate passes.  Small ones, and many, keep the two-axis passes, and
+    MIFFT_PLANES=1 takes them wherever they fit."""
+    lists, _ = _lists(shape, kind, prec)
+    assert not [k for k in lists if k.startswith("plane_")]
+    monkeypatch.setenv("MIFFT_PLANES", "1")
+    lists, _ = _lists(shape, kind, prec)
+    assert lists["plane_forward"] and lists["plane_inverse"]
+    monkeypatch.delenv("MIFFT_PLANES")
+    for s, k, pr in (((2, 64, 64), 0, 0), ((64, 64, 64), 0, 1), ((32, 32, 32), 0, 1), ((200, 128, 128), 0, 0),
+                     ((1024, 60, 300), 1, 0)):
+        assert _lists(s, k, pr)[0]["plane_forward"]
