@@ -567,8 +567,14 @@ __device__ __forceinline__ void plane_tables(const PlaneArgs<T>& a, int L, cx<T>
     x.rev = rev;
 }
 
-// Row pitch of the tile: a line's padded places, or its L + 1 outputs.
-constexpr int plane_pitch(int L, const PlaneRadices& f) { return L + (L >> line_shift(f)) + 1; }
+// Row pitch of the tile: a line's padded places, or its L + 1 outputs; not a
+// multiple of 16 elements, which would put the rows of a wavefront's lines on
+// the same banks (15-point lines, a row per lane: 486 x 200 x 30 R2C 38 us).
+constexpr int plane_pitch(int L, const PlaneRadices& f)
+{
+    const int p = L + (L >> line_shift(f)) + 1;
+    return p % 16 == 0 ? p + 1 : p;
+}
 
 // Rows of a wavefront: LPW lines at a time; lanes past the last line repeat
 // the first line's threads (same values to the same places), and so do rows

@@ -219,3 +219,15 @@ def test_few_large_planes_keep_the_one_axis_passes(monkeypatch, shape, kind, pre
     for s, k, pr in (((2, 64, 64), 0, 0), ((64, 64, 64), 0, 1), ((32, 32, 32), 0, 1), ((200, 128, 128), 0, 0),
                      ((1024, 60, 300), 1, 0)):
         assert _lists(s, k, pr)[0]["plane_forward"]
+
+
+def test_plane_rows_do_not_share_banks():
+    """The rows of a wavefront's lines are no multiple of 16 elements apart in
+    LDS (tile, two twiddle tables, digit reversal, split factors make its size)."""
+    for n2 in (15, 30, 48, 60, 90, 96, 120, 128, 150, 240, 256):
+        for prec in (0, 1):
+            p = _lists((1024, 20, n2), 0, prec)[0]["plane_forward"][0]
+            assert p["kind"] == "plane" and p["nb"] == 1
+            A, L, esz = p["rows"], p["L"], 16 if prec else 8
+            pitch, rest = divmod(p["lds"] // esz - L - 2 * A - (A + 3) // 4, A)
+            assert rest == 0 and pitch > L and pitch % 16 != 0, (n2, prec, pitch)
