@@ -2026,7 +2026,10 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
             double rows = row >= 128 ? 1.0 : inner ? 1.2 : (size_t)nc * plan.esz % 128 == 0 ? 1.1 : 1.25;
             if (inner) rows *= (double)((nc + C - 1) / C * C) / nc;
             const double wide = cols_threads(plan, B, C, 1 << 20) > 512 ? 0.05 : 0.0; // sixteen wavefronts fill a CU
-            const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (2 * cl > kLdsMax ? 1.2 : 1.0 + wide) * rows * stages;
+            // a tile of more than 512 threads takes a CU's registers: alone there too, where there are more tiles than CUs
+            const long long ct = (long long)plan.n1 / B * nc / C;
+            const bool alone = 2 * cl > kLdsMax || (ct * plan.copies > plan.cus && cols_threads(plan, B, C, ct) > 512);
+            const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (alone ? 1.2 : 1.0 + wide) * rows * stages;
             if (cost < best || (cost == best && cl > best_cl)) { // the larger tile: less set-up
                 best = cost;
                 best_cl = cl;

@@ -231,3 +231,14 @@ def test_plane_rows_do_not_share_banks():
             A, L, esz = p["rows"], p["L"], 16 if prec else 8
             pitch, rest = divmod(p["lds"] // esz - L - 2 * A - (A + 3) // 4, A)
             assert rest == 0 and pitch > L and pitch % 16 != 0, (n2, prec, pitch)
+
+
+@pytest.mark.parametrize("shape,kind", [((72, 160, 288), 0), ((72, 216, 180), 0), ((100, 150, 576), 1), ((96, 120, 864), 1)])
+def test_wide_columns_tiles_count_as_alone(shape, kind):
+    """More than 512 threads take a CU's registers: with more tiles than CUs,
+    such a tile is weighed as one that is alone there, and narrower ones or the
+    one-axis passes run."""
+    lists, _ = _lists(shape, kind, 0)
+    for name in ("plane_forward", "plane_inverse"):
+        for p in lists.get(name, []):
+            assert p["kind"] != "cols" or p["block"] <= 512
