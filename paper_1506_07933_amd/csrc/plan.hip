@@ -1881,10 +1881,12 @@ static unsigned cols_grid(const Pass& p, int ng)
 // one workgroup as well, from 48 KiB on, or from 28 KiB where FP32 z-lines
 // take radices above 8 and so few threads (30 x 60 x 300 R2C 15 against 20 us, 12 x 20 x
 // 750 Poisson 22 against 27; above the lines on average 1.06 times, below 0.92;
-// 2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64 15.7 against 13.5).
+// 2 x 64 x 64 14.0 against 11.2 us, 64 x 64 x 64 FP64 15.7 against 13.5).  A grouped batch
+// fills the device with fewer planes of each member, but its members give the
+// bits of single transforms, so they run the same passes.
 static bool plane_pays(const Plan& plan, int L, size_t lds, long long tiles, bool split)
 {
-    const long long t4 = 4 * tiles * plan.copies;
+    const long long t4 = 4 * tiles;
     const bool wide = plan.prec == MIFFT_FP32 && radices_of(L, plan.prec).r[0] > 8;
     return plan.plane_force || (!(2 * lds > kLdsMax && t4 < (split ? 2LL : 3LL) * plan.cus) &&
                                 !(lds > (wide ? 28 : 48) * 1024 && t4 < plan.cus));
@@ -1980,7 +1982,7 @@ static int cols_threads(const Plan& plan, int B, int C, long long tiles)
 {
     const int P = B * C, slots = kColsHeld / (int)plan.esz / B; // rows of C per thread
     for (int want : {512, 1024}) {
-        if (want == 512 && (2 * cols_lds(plan, B, C) > kLdsMax || tiles * plan.copies <= plan.cus)) continue;
+        if (want == 512 && (2 * cols_lds(plan, B, C) > kLdsMax || tiles <= plan.cus)) continue;
         const int t = std::min(want, plan.n0 * P) / P * P;
         if (t > 0 && slots * (t / C) >= plan.n0) return t;
     }
@@ -2028,7 +2030,7 @@ static bool choose_split(const Plan& plan, int L, int nc, bool inner, Split* s)
             const double wide = cols_threads(plan, B, C, 1 << 20) > 512 ? 0.05 : 0.0; // sixteen wavefronts fill a CU
             // a tile of more than 512 threads takes a CU's registers: alone there too, where there are more tiles than CUs
             const long long ct = (long long)plan.n1 / B * nc / C;
-            const bool alone = 2 * cl > kLdsMax || (ct * plan.copies > plan.cus && cols_threads(plan, B, C, ct) > 512);
+            const bool alone = 2 * cl > kLdsMax || (ct > plan.cus && cols_threads(plan, B, C, ct) > 512);
             const double cost = (2 * pl > kLdsMax ? 1.12 : 1.0) + (alone ? 1.2 : 1.0 + wide) * rows * stages;
             if (cost < best || (cost == best && cl > best_cl)) { // the larger tile: less set-up
                 best = cost;
@@ -2067,7 +2069,7 @@ static int build_split(Plan& plan)
     // 4 MiB (5 x 125 x 100 FP64 13.5 us against 12.7) and not where the columns
     // pass leaves most of the device idle (64 x 96 x 128 FP32 18.5 against 18.8).
     auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
-    if (!W && !getenv("MIFFT_SPLIT")) {
+    if (!W && !getenv("MIFFT_SPLIT") && !plan.plane_force) {
         if (cols_threads(plan, B, sp.C, 1 << 20) > 512) return MIFFT_OK;
         const long long bytes = (long long)n0 * n1 * nc * (long long)plan.esz;
         if (!real && ((pow2(n1) && pow2(plan.n2)) || bytes < (4LL << 20) || 2LL * A * nc / sp.C < plan.cus))
@@ -2154,7 +2156,7 @@ static int build_split(Plan& plan)
         c.ntiles = c.flat ? (int)(((long long)A * nc + sp.C - 1) / sp.C) : A * c.tpg;
         c.shmem = cols_lds(plan, B, sp.C);
         c.xcd = c.ntiles % 8 == 0;
-        c.block = (unsigned)cols_threads(plan, B, sp.C, (long long)A * nc / sp.C);
+        c.block = (unsigned)cols_threads(plan, B, sp.C, (long long)A * nc / sp.C * plan.copies);
         const size_t out_bytes = (size_t)n0 * plane * plan.esz;
         a.nt_out = c2r && out_bytes >= ((size_t)128 << 20);
         c.nt_out = out_bytes > ((size_t)256 << 20);

@@ -217,10 +217,12 @@ def test_persistent_plane_items(prec):
 
 
 @pytest.mark.parametrize("mode,shape,together", [("kernels", (64, 128, 128), 1), ("grouped", (64, 128, 128), 4),
-                                                 ("grouped", (4, 256, 128), 1), ("kernels", (4, 256, 128), 1)])
-def test_schedules_count_only_what_runs_together(mode, shape, together):
-    """The planner chooses for the tiles of one launch: a batch of per-pass
-    kernels, and transforms that need a workspace, run one by one."""
+                                                 ("grouped", (4, 256, 128), 1), ("kernels", (4, 256, 128), 1),
+                                                 ("grouped", (48, 64, 96), 4), ("grouped", (20, 96, 90), 4)])
+def test_batches_of_plans_run_the_schedule_of_single_transforms(mode, shape, together):
+    """How many transforms run together (one by one in a batch of per-pass
+    kernels, and where they need a workspace) shapes the launches, not the
+    passes: every mode gives the bits of single transforms."""
     from paper_1506_07933_amd import BatchPlan, Plan
     xs = [torch.from_numpy(synth.uniform_complex(shape, np.complex64, seed=i)).cuda() for i in range(4)]
     b = BatchPlan([shape] * 4, "fp32", mode=mode)
@@ -228,10 +230,7 @@ def test_schedules_count_only_what_runs_together(mode, shape, together):
     outs = b.forward(xs)
     p = Plan(shape, "c2c", "fp32")
     for x, o in zip(xs, outs):
-        if together == 1:
-            assert torch.equal(o, p.forward(x))
-        else:
-            assert rel_l2(o.cpu().numpy(), oracle.fft3d_c2c(x.cpu().numpy().astype(np.complex128), -1)) <= TOL["fp32"]
+        assert torch.equal(o, p.forward(x))
     p.close()
     b.close()
 
@@ -409,10 +408,7 @@ def test_in_place_split_calls_need_no_memory_and_agree(monkeypatch, split, shape
         b = BatchPlan([shape] * 3, prec, mode=mode)
         xs = [x.clone(), x2.clone(), x.clone()]
         b.forward(xs, [xs[0], torch.empty_like(x2), xs[2]])
-        assert torch.equal(xs[0], xs[2]) and torch.equal(xs[1], x2)
-        if mode == "kernels" or split:  # (grouped launches may choose another schedule for their tiles)
-            assert torch.equal(xs[0], Z)
-        assert rel_l2(xs[0].cpu().numpy(), X.cpu().numpy()) <= TOL[prec]
+        assert torch.equal(xs[0], Z) and torch.equal(xs[2], Z) and torch.equal(xs[1], x2)
         b.close()
 
 
