@@ -17,7 +17,9 @@
 // tile's loads are in flight meanwhile (2-4%).  Consecutive tiles share cache
 // lines where rows are not whole lines (129 columns) or a tile's rows are
 // half lines; each XCD therefore takes consecutive tiles (256^3 FP32, 64-byte
-// rows: C2C 133 -> 112 us a transform, R2C 87 -> 77).
+// rows: C2C 133 -> 112 us a transform, R2C 87 -> 77) where their number divides
+// by 8; other numbers keep the round-robin order, which has not been timed
+// against a padded index.
 #pragma once
 
 #include "plane.hpp"
@@ -414,7 +416,9 @@ template <typename T> __global__ __launch_bounds__(1024) void k_cols_mid(MidArgs
     const int kb = x.p / a.C;
     __syncthreads();
     const V none{T(1), T(0)};
-    // (the next tile's loads held through both transforms would not fit 128 registers)
+    // (the next tile's loads held through both transforms would not fit 128
+    // registers; as it is, FP32 keeps two of each thread's in scratch memory,
+    // stored once and reloaded once per tile)
     for (int i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
         int g, col;
         const bool valid = cols_locate(a, x.c, i, g, col);

@@ -2066,8 +2066,9 @@ static int build_split(Plan& plan)
     // 128^3 FP64 R2C 35.7 against 29.3; a columns tile alone on its CU: 125^3 35.1
     // against 37.8.  C2C calls in place run the one-axis passes, whose rounding
     // differs: the split has to save more than launches for that, so not below
-    // 4 MiB (5 x 125 x 100 FP64 13.5 us against 12.7) and not where the columns
-    // pass leaves most of the device idle (64 x 96 x 128 FP32 18.5 against 18.8).
+    // 4 MiB (5 x 125 x 100 FP64 13.5 us against 12.7, the split through a workspace in
+    // both) and not where the columns pass leaves most of the device idle (64 x 96 x
+    // 128 FP32, likewise, 18.5 against 18.8).
     auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
     if (!W && !getenv("MIFFT_SPLIT") && !plan.plane_force) {
         if (cols_threads(plan, B, sp.C, 1 << 20) > 512) return MIFFT_OK;

@@ -21,7 +21,7 @@
 // loaded from, any place.
 //
 // What bounds it: large batches of planes, HBM and the vector units together
-// (512 x 256 planes of 128 x 64 complex64, two 76 KiB workgroups per CU: 3.3 ms
+// (512 x 256 planes of 128 x 64 complex64, two 72 KiB workgroups per CU: 3.3 ms
 // against 2.7 + 2.9 ms for the two passes it replaces, 5.1 TB/s; about 50
 // instructions per element); few planes, one workgroup's latency (7 us for
 // 32 x 32, 11 us for 128 x 128), against two launches of 4.5 us and more.
