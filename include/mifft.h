@@ -43,7 +43,10 @@
  *   MIFFT_STRIDED_PERSIST=0   one workgroup per column tile instead of a resident grid
  *   MIFFT_PAD_ROWS=0          unpadded rows in the internal transposed intermediate
  *   MIFFT_POISSON_UNFUSED=1   Poisson solve with a standalone multiply pass
- *   MIFFT_BATCH_ITEM_KIB      data per work item of the persistent batch (default 64)
+ *   MIFFT_PLANES=0 | 1        one axis per pass throughout (no plane or split-axis passes, no plane
+ *                             items) | plane passes wherever they fit (default: where they pay)
+ *   MIFFT_SPLIT=B,C           y-axis split with that B and C columns per tile where it fits
+ *   MIFFT_BATCH_ITEM_KIB      data per work item of the persistent batch (default 128; 256 with plane items)
  *   MIFFT_BATCH_PUBLISH_EVERY publish batch completions after this many items (default: never early)
  * They select among equivalent schedules (for measurement); results agree
  * within rounding.
@@ -78,7 +81,12 @@ typedef enum {
 #define MIFFT_TUNE 1u      /* time the candidate variants on the device and keep the
                               fastest (in the spirit of the MEASURE planning the paper
                               uses, Sec. 3, Implementation Details); consults and
-                              updates the wisdom file named by MIFFT_WISDOM */
+                              updates the wisdom file named by MIFFT_WISDOM.  The
+                              candidates are passes of one axis each: the passes of two
+                              axes that untuned plans (and untuned persistent batches)
+                              run where they pay are not among them, so a tuned plan or
+                              batch may be the slower one (64 uneven FP32 transforms:
+                              0.96 ms tuned, 0.71 ms untuned) */
 
 #define MIFFT_BATCH_KERNELS 4u /* batches: run the per-pass kernels of ordinary plans instead of
                                   the persistent kernel (any supported length) */
@@ -122,7 +130,9 @@ int mifft_plan_create(mifft_plan* out, int n0, int n1, int n2, int kind, int pre
 /*
  * mifft_execute_forward -- forward transform (Algorithm 1, left column:
  * z-FFT, y-FFT, x-FFT; at P0 = P1 = 1 both exchanges are identities).
- *   C2C: in, out complex [n0][n1][n2]; in == out is allowed.
+ *   C2C: in, out complex [n0][n1][n2]; in == out is allowed (with no more
+ *        workspace than mifft_workspace_bytes; plans that report none may run
+ *        other passes in place than out of place, and then round differently).
  *   R2C: in real [n0][n1][n2], out complex [n0][n1][n2/2+1]; must not overlap.
  * `in` is not modified unless in == out.  Uses the plan's default workspace.
  */
@@ -363,8 +373,9 @@ int mifft_batch_destroy(mifft_batch batch);
  * outputs of that launch are not valid; 0 otherwise. */
 int mifft_batch_check(mifft_batch batch, int* aborted);
 
-/* Writes a one-line description of the batch (mode, passes, work items,
- * persistent grid, LDS) into buf. */
+/* Writes a description of the batch into buf: a line for its mode, passes,
+ * work items, persistent grid and LDS, then one per (stage, length) and per
+ * plane shape, or per shape of a batch of ordinary plans. */
 int mifft_batch_describe(mifft_batch batch, char* buf, size_t len);
 
 /*
